@@ -304,3 +304,106 @@ def tolerance(case):
     if case["op"] == "compress":
         return {"rel": 1e-5, "max": 1e-2} if bf16 else {"rel": 1e-6, "max": 1e-5}
     return {"rel": 9e-3, "max": 0.06, "differ": 0.005} if bf16 else {"rel": 2e-6, "max": 1e-5, "differ": 0.005}
+
+
+# ---- the same outputs in 64 bits ------------------------------------------------------------------------------------
+def _attend(q, k, v, visible, scale):
+    """q [.., R, d_k], k [.., N, d_k], v [.., N, d_v], visible [.., R or 1, N]: (output, probabilities); a row that sees nothing is 0."""
+    s = (q @ k.transpose(-1, -2).contiguous() * scale).masked_fill(~visible, -math.inf)
+    m = s.amax(-1, keepdim=True)
+    p = torch.exp(s - torch.where(torch.isinf(m), torch.zeros_like(m), m))
+    z = p.sum(-1, keepdim=True)
+    p = p / torch.where(z == 0, torch.ones_like(z), z)
+    return p @ v, p
+
+
+def _select(imp, own, n_sel):
+    """imp [t, hk, nblk], own [t]: per query and KV head the forced blocks, then the best; -1 padded."""
+    t, hk, nblk = imp.shape
+    blk, own = torch.arange(nblk, device=imp.device).view(1, 1, nblk), own.view(t, 1, 1)
+    score = torch.where((blk < N_INIT) | (blk > own - N_LOCAL), torch.full_like(imp, 1e9), imp)
+    score = torch.where(blk > own, torch.full_like(score, -1.0), score)
+    top, idx = score.sort(dim=-1, descending=True, stable=True)
+    return torch.where(top < 0, torch.full_like(idx, -1), idx)[..., :n_sel]
+
+
+def _exact_compress(s):
+    out = []
+    for x, c in ((s["k"], s["k_cmp"]), (s["v"], s["v_cmp"])):
+        y = c.double()
+        for b, after in enumerate(s["after"].tolist()):
+            lo, hi = _cmp_rows(int(s["before"][b])) if s["before"] is not None else 0, _cmp_rows(after)
+            if hi > lo:
+                y[b, :, lo:hi] = x[b, :, lo * STRIDE:(hi - 1) * STRIDE + L_CMP].double().unfold(1, L_CMP, STRIDE).mean(-1)
+        out.append(y)
+    return out[0], out[1], None
+
+
+def exact(case, seed):
+    """The definition, query by query, in 64 bits.  The indices have no such value (a tie may fall either way)."""
+    s = prepare(case, seed)
+    if case["op"] == "compress":
+        return _exact_compress(s)
+    dev, t, h, hk = s["q"].device, case["queries"], case["heads"], case["kv_heads"]
+    hg, scale = h // hk, 1.0 / math.sqrt(case["d_k"])
+    parents = list(range(-1, t - 1)) if case["drafts"] == "chain" else _tree(case["drafts"])[0]
+    depth, seen = [], torch.zeros((t, t), dtype=torch.bool)
+    for i, p in enumerate(parents):
+        depth.append(0 if p < 0 else depth[p] + 1)
+        if p >= 0:
+            seen[i] = seen[p]
+        seen[i, i] = True
+    seen, depth = seen.to(dev), torch.tensor(depth, device=dev)
+    out = torch.zeros(s["out"].shape, dtype=torch.float64, device=dev)
+    by_group = lambda x: x.view(-1, hk, hg, x.shape[-1])                       # [t, hk, hg, d]
+    for b, (length, nq) in enumerate(zip(s["seq_lens"].tolist(), s["n_query"].tolist())):
+        nc, rows = int(s["n_cmp"][b]), length + nq
+        q = by_group(s["q"][b, :nq].double())
+        gates = s["gates"][b, :nq].double().view(nq, hk, hg, 3)
+        slot = torch.arange(rows, device=dev)
+        draft = (slot - length).clamp(min=0)
+        sees = (slot < length) | seen[:nq][:, draft]                           # [nq, rows]
+        pos = torch.where(slot < length, slot, length + depth[draft])
+        own_pos = length + depth[:nq]
+        # compressed branch (its rows hold committed tokens only) and the importance of every block
+        nblk = rows // L_SEL + 1
+        imp = torch.zeros((nq, hk, nblk), dtype=torch.float64, device=dev)
+        if nc:
+            flat = q.permute(1, 0, 2, 3).reshape(hk, nq * hg, -1)
+            o, p = _attend(flat, s["k_cmp"][b, :, :nc].double(), s["v_cmp"][b, :, :nc].double(),
+                           torch.ones((1, 1, nc), dtype=torch.bool, device=dev), scale)
+            o = o.view(hk, nq, hg, -1).permute(1, 0, 2, 3)
+            p = p.view(hk, nq, hg, nc).sum(2).permute(1, 0, 2)
+            per = L_SEL // STRIDE
+            for m in range(per):
+                for n in range(L_CMP // STRIDE):
+                    c = torch.arange(nblk, device=dev) * per + m - n
+                    ok = (c >= 0) & (c < nc)
+                    imp += torch.where(ok, p[..., c.clamp(0, nc - 1)], torch.zeros_like(imp))
+            acc = gates[..., 0:1] * o
+        else:
+            acc = torch.zeros((nq, hk, hg, case["d_v"]), dtype=torch.float64, device=dev)
+        if case["mode"] == "reuse":
+            sel = s["sel_idx"][b, :nq].long()
+        else:
+            sel = _select(imp, (length + torch.arange(nq, device=dev)) // L_SEL, case["n_sel"])
+            if case["mode"] == "shared":                                       # the deepest (last) member's set for the whole run
+                run_len = max(1, min(t, 64 // hg))
+                for lo in range(0, nq, run_len):
+                    d = depth[lo:min(lo + run_len, nq)].tolist()
+                    sel[lo:lo + len(d)] = sel[lo + max(range(len(d)), key=lambda i: (d[i], i))].clone()
+        k, v = s["k"][b], s["v"][b]                                            # [hk, rows, d]
+        head = torch.arange(hk, device=dev).view(1, hk, 1)
+        for lo in range(0, nq, 16):                                            # queries at a time
+            qs = slice(lo, min(lo + 16, nq))
+            x = sel[qs]
+            tok = (x.clamp(min=0).unsqueeze(-1) * L_SEL + torch.arange(L_SEL, device=dev)).flatten(2)
+            ok = (x >= 0).repeat_interleave(L_SEL, -1) & (tok < rows)
+            tok = tok.clamp(max=rows - 1)
+            ok = ok & torch.gather(sees[qs].unsqueeze(1).expand(-1, hk, -1), 2, tok)
+            acc[qs] += gates[qs, ..., 1:2] * _attend(q[qs], k[head, tok].double(), v[head, tok].double(), ok.unsqueeze(2), scale)[0]
+        lo = max(0, length - case["window"])
+        near = (sees & (pos > own_pos.view(-1, 1) - case["window"]) & (pos <= own_pos.view(-1, 1)))[:, lo:].view(nq, 1, 1, -1)
+        acc += gates[..., 2:3] * _attend(q, k[:, lo:rows].double(), v[:, lo:rows].double(), near, scale)[0]
+        out[b, :nq] = acc.reshape(nq, h, -1)
+    return out, None
