@@ -23,17 +23,29 @@ struct CombineArgs {
     int T, H;
     int n_cmp_chunks, n_win_splits, n_slc_splits;
     int64_t rows_total;
+    FastDiv div_H, div_T;
     int64_t out_s[3];     // bytes: sequence, query, head
     // k_combine_rows only: branches [br_lo, br_hi) in gate order (compressed, selected, window) are merged; with
     // use_gates == 0 their normalised sum is written as it is (one branch: that branch's output)
     int br_lo, br_hi, use_gates;
 };
 
+// These launches take 5 us at a few hundred rows and are a chain of latencies: the arguments, the row's place in the batch
+// (64-bit divisions by run-time sizes cost about 0.5 us of it), the statistics, the accumulators.  Multiplications in
+// place of the divisions and one round trip for the arguments took the reuse call at 32K tokens and 8 queries from
+// 17.5 to 17.0 us and the 64-query chain of 32 heads from 64.0 to 62.3 us.
+// (sequence, query, head) of an output row; rows are fewer than 2^31 (their partial states alone would be a terabyte)
+struct RowOf { int64_t b; int i, h; };
+template <typename Args>
+__device__ __forceinline__ RowOf row_of(const Args& a, int64_t row) {
+    const int bi = a.div_H.div((int)row), b = a.div_T.div(bi);
+    return RowOf{b, bi - b * a.T, (int)row - bi * a.H};
+}
+
 // byte offset of output row (b, i, h)
 __device__ __forceinline__ int64_t out_row_offset(const CombineArgs& a, int64_t row) {
-    const int h = (int)(row % a.H), i = (int)((row / a.H) % a.T);
-    const int64_t b = row / ((int64_t)a.H * a.T);
-    return b * a.out_s[0] + i * a.out_s[1] + h * a.out_s[2];
+    const RowOf r = row_of(a, row);
+    return r.b * a.out_s[0] + r.i * a.out_s[1] + r.h * a.out_s[2];
 }
 
 constexpr int kMaxSlotsPerBranch = 64;      // compressed scan; the other two branches: 32 each
@@ -44,6 +56,7 @@ constexpr int kCombineRowsMaxSlots = 16;   // slices per row up to which a threa
 // Every load is issued at once (one memory round trip: these calls are small and bound by latency).
 template <bool BF16, int DV>
 __global__ void __launch_bounds__(kThreads) k_combine_rows(const CombineArgs a) {
+    touch_args<CombineArgs>();
     constexpr int TPR = DV / 4;                 // threads across one row, 4 columns each
     constexpr int RPW = kThreads / TPR;         // rows per workgroup
     constexpr int MS = kCombineRowsMaxSlots;
@@ -51,8 +64,8 @@ __global__ void __launch_bounds__(kThreads) k_combine_rows(const CombineArgs a) 
     const int64_t row = (int64_t)blockIdx.x * RPW + tid / TPR;
     if (row >= a.rows_total) return;
     const int c = tid % TPR;
-    const int i = (int)((row / a.H) % a.T);
-    const int b = (int)(row / ((int64_t)a.H * a.T));
+    const RowOf rw = row_of(a, row);
+    const int i = rw.i, b = (int)rw.b;
     // slot ranges: cmp [0, n_cmp), win [n_cmp, n_cmp + n_win), slc after; gate order: cmp, slc, win
     const int lo3[3] = {0, a.n_cmp_chunks + a.n_win_splits, a.n_cmp_chunks};
     const int cnt3[3] = {a.n_cmp_chunks, a.n_slc_splits, a.n_win_splits};
@@ -119,6 +132,7 @@ __global__ void __launch_bounds__(kThreads) k_combine_rows(const CombineArgs a) 
 // weights after it: one memory round trip per batch instead of two, and no start-up per batch.
 template <bool BF16, int DV>
 __global__ void __launch_bounds__(kThreads) k_combine_stream(const CombineArgs a) {
+    touch_args<CombineArgs>();
     constexpr int TPR = DV / 4;                 // threads across one row, 4 columns each
     constexpr int RPW = kThreads / TPR;         // rows per batch
     constexpr int MS = kCombineRowsMaxSlots;
@@ -136,8 +150,8 @@ __global__ void __launch_bounds__(kThreads) k_combine_stream(const CombineArgs a
         Fetched f{make_float2(0.f, 0.f), 0.f, false};
         const int64_t row = batch * RPW + wr;
         if (wlane && batch < n_batches && row < a.rows_total) {
-            const int i = (int)((row / a.H) % a.T);
-            const int b = (int)(row / ((int64_t)a.H * a.T));
+            const RowOf rw = row_of(a, row);
+            const int i = rw.i, b = (int)rw.b;
             const int Tq = a.n_query ? min(max(a.n_query[b], 0), a.T) : a.T;
             f.st = *reinterpret_cast<const float2*>(a.part_stats + ((int64_t)ws * a.rows_total + row) * 2);
             f.gate = a.gates[row * 3 + wbr];
@@ -221,33 +235,39 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
 
 template <bool BF16, int DV>
 __global__ void __launch_bounds__(kThreads) k_combine_slices(const CombineArgs a) {
+    touch_args<CombineArgs>();
     constexpr int TPR = DV / 4;                 // threads across one row, 4 columns each
     constexpr int SL = kThreads / TPR;          // slices accumulated in parallel
     __shared__ float s_w[kMaxSlotsTotal];
     __shared__ f32x4 s_red[SL][TPR];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t row = blockIdx.x;
-    const int i = (int)((row / a.H) % a.T);
-    const int b = (int)(row / ((int64_t)a.H * a.T));
+    const RowOf rw = row_of(a, row);
+    const int i = rw.i, b = (int)rw.b;
     const int Tq = a.n_query ? min(max(a.n_query[b], 0), a.T) : a.T;
     const int n_slots = a.n_cmp_chunks + a.n_win_splits + a.n_slc_splits;
     const int c = tid % TPR, sl = tid / TPR;
 
+    // (The statistics and the gate do not wait for the query count.  Fetching the first accumulators together with them, too,
+    // was slower where batches of mixed lengths leave slices empty: 43.7 against 44.3 us for five sequences of 3K to 40K.)
+    // wavefronts 0..2 take one branch each; slot ranges: cmp [0, n_cmp), win [n_cmp, n_cmp + n_win), slc after; gate
+    // order: cmp, slc, win
+    const int lo = wave == 0 ? 0 : (wave == 1 ? a.n_cmp_chunks + a.n_win_splits : a.n_cmp_chunks);
+    const int cnt = wave == 0 ? a.n_cmp_chunks : (wave == 1 ? a.n_slc_splits : (wave == 2 ? a.n_win_splits : 0));
+    float2 st = make_float2(0.f, 0.f);
+    float gate = 0.f;
+    if (wave < 3) {
+        if (lane < cnt) st = *reinterpret_cast<const float2*>(a.part_stats + ((int64_t)(lo + lane) * a.rows_total + row) * 2);
+        gate = a.gates[row * 3 + wave];
+    }
+
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     if (i < Tq) {     // uniform per workgroup
         if (wave < 3) {
-            // slot ranges: cmp [0, n_cmp), win [n_cmp, n_cmp + n_win), slc after; gate order: cmp, slc, win
-            const int lo = wave == 0 ? 0 : (wave == 1 ? a.n_cmp_chunks + a.n_win_splits : a.n_cmp_chunks);
-            const int cnt = wave == 0 ? a.n_cmp_chunks : (wave == 1 ? a.n_slc_splits : a.n_win_splits);
-            float m = -INFINITY, z = 0.f;
-            if (lane < cnt) {
-                const float2 st = *reinterpret_cast<const float2*>(a.part_stats + ((int64_t)(lo + lane) * a.rows_total + row) * 2);
-                if (st.y > 0.f) { m = st.x; z = st.y; }
-            }
-            const float M = wave_max_f32(m);
-            const float e = z > 0.f ? fast_exp2(m - M) : 0.f;
-            const float Zt = wave_sum_f32(e * z);
-            const float gate = a.gates[row * 3 + wave];
+            const bool live = st.y > 0.f;
+            const float M = wave_max_f32(live ? st.x : -INFINITY);
+            const float e = live ? fast_exp2(st.x - M) : 0.f;
+            const float Zt = wave_sum_f32(live ? e * st.y : 0.f);
             if (lane < cnt) s_w[lo + lane] = Zt > 0.f ? gate * e / Zt : 0.f;
         }
         __syncthreads();
@@ -294,19 +314,22 @@ struct GateArgs {
     const int32_t* n_query;
     void* out;
     int T, H;
+    FastDiv div_H, div_T;
     int64_t rows_total;
     int64_t out_s[3];
 };
 
 template <bool BF16, int DV>
 __global__ void __launch_bounds__(kThreads) k_gate(const GateArgs a) {
+    touch_args<GateArgs>();
     constexpr int TPR = DV / 4, RPW = kThreads / TPR;
     const int tid = threadIdx.x;
     const int64_t row = (int64_t)blockIdx.x * RPW + tid / TPR;
     if (row >= a.rows_total) return;
     const int c = tid % TPR;
-    const int h = (int)(row % a.H), i = (int)((row / a.H) % a.T);
-    const int64_t b = row / ((int64_t)a.H * a.T);
+    const RowOf rw = row_of(a, row);
+    const int h = rw.h, i = rw.i;
+    const int64_t b = rw.b;
     const int Tq = a.n_query ? min(max(a.n_query[b], 0), a.T) : a.T;
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     if (i < Tq) {

@@ -626,7 +626,8 @@ int launch_all(const void* q, const void* k, const void* v, const void* kc, cons
 
     CombineArgs ca{};
     ca.part_stats = part_stats; ca.part_acc = part_acc; ca.gates = gates; ca.n_query = n_query; ca.out = out;
-    ca.T = p->T; ca.H = p->H; ca.n_cmp_chunks = pl.n_cmp_chunks; ca.n_win_splits = pl.n_win_splits;
+    ca.T = p->T; ca.H = p->H; ca.div_H = FastDiv::of(p->H); ca.div_T = FastDiv::of(p->T);
+    ca.n_cmp_chunks = pl.n_cmp_chunks; ca.n_win_splits = pl.n_win_splits;
     ca.n_slc_splits = pl.n_slc_splits; ca.rows_total = lo.rows_total;
     ca.br_lo = 0; ca.br_hi = 3; ca.use_gates = 1;
     for (int j = 0; j < 3; ++j) ca.out_s[j] = lo.out_s[j];
@@ -656,7 +657,8 @@ int launch_all(const void* q, const void* k, const void* v, const void* kc, cons
         if (launch_stream(SSV_K_STREAM_W, kRolesWin, pl.n_cmp_chunks, pl.n_win_splits, 1, p->T) || branch_out(SSV_K_OUT_WIN, 2)) return SSV_ELAUNCH;
         GateArgs ga{};
         ga.o_cmp = branch; ga.o_slc = branch + lo.branch_bytes; ga.o_win = branch + 2 * lo.branch_bytes;
-        ga.gates = gates; ga.n_query = n_query; ga.out = out; ga.T = p->T; ga.H = p->H; ga.rows_total = lo.rows_total;
+        ga.gates = gates; ga.n_query = n_query; ga.out = out; ga.T = p->T; ga.H = p->H;
+        ga.div_H = ca.div_H; ga.div_T = ca.div_T; ga.rows_total = lo.rows_total;
         for (int j = 0; j < 3; ++j) ga.out_s[j] = lo.out_s[j];
         if (tm.begin(SSV_K_COMBINE)) return SSV_ELAUNCH;
         for (int r = 0; r < reps; ++r) SSV_LAUNCH(SSV_K_COMBINE, (k_gate<BF16, DV>), grid_rows, 0, ga);
