@@ -37,6 +37,7 @@ constexpr int kResidentWgs = 256 * 2;        // workgroups one round holds: LDS 
 constexpr int kMinTilesPerSlice = 2;
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
+constexpr int kJointMaxTiles = 160;          // window tiles and schedule entries that one workgroup of the joint launch takes, at most
 constexpr int kImportanceWgs = 512;          // one round of the importance pass (more, shorter workgroups measured slower)
 constexpr int kTopnInSlcMaxWgs = 256;        // SSV_TOPN_AUTO: select inside the selected-branch launch up to this many workgroups
                                              // (twice as many when a wavefront has one query to select for)
@@ -75,7 +76,8 @@ void stream_tile_lds(bool bf16, int d_k, int d_v, size_t* lds_k, size_t* lds_vt)
     *lds_vt = bf16 ? (size_t)kTile * (d_v * 2 + 32) : (size_t)d_v * (kTile * 4 + 16);
 }
 
-int make_layout(const ssv_nsa_params* p, Layout* lo) {
+// few_slots: no branch gets more slots for being cut together with the other
+int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     if (!p) return SSV_EINVAL;
     if (p->B < 1 || p->T < 1 || p->H < 1 || p->H_kv < 1 || p->d_k < 1 || p->d_v < 1) return SSV_EINVAL;
     if (p->H % p->H_kv) return SSV_EINVAL;
@@ -256,19 +258,34 @@ int make_layout(const ssv_nsa_params* p, Layout* lo) {
     pl.n_slc_splits = std::min(std::max(1, ceil_div(nts, per_s)), cap_ws);
     lo->joint_parts = 0;
     if (lo->scan32) {
-        // One round of resident workgroups: the parts of a group are cut over window tiles and schedule entries together,
-        // and every part owns a window slot and a selected slot (the one its tiles do not reach stays empty); measured
-        // 3 us faster at a 40-node tree over 128K tokens, where the window's own workgroup would sit idle for half the
-        // launch.  Several rounds fill such gaps by themselves (32 mixed-length sequences: 2 us slower): separate slices.
-        const int parts = std::min(std::max(1, ceil_div(ntw + nts, per_s)), kCombineRowsMaxSlots / 2);
-        if (units * parts <= kResidentWgs) {
+        // The parts of a group are cut over window tiles and schedule entries together, and every part owns a window slot and
+        // a selected slot (the one its tiles do not reach stays empty): no workgroup sits idle behind the window's few tiles,
+        // a group starts up and writes its states as few times as possible, and with one round the selection runs inside
+        // the launch.  As many parts as one round of resident workgroups takes; where that is fewer than the
+        // slice length asks for, parts hold at most kJointMaxTiles tiles, and a single part per group is taken in batches of mixed lengths only, where the rounds,
+        // last one included, are 85 % full: nothing evens out workgroups this long.
+        // Whole calls against separate slices per branch (refresh, 4K..128K tokens, 16 queries; groups x parts of 512 places):
+        // 192 x 2 162 -> 154 us, 256 x 2 188 -> 176, 448 x 1 270 -> 261, 512 x 1 295 -> 283, 1024 x 1 533 -> 519;
+        // 40-node trees over 64K: 240 x 2 205 -> 177.  Beyond the line separate slices stay
+        // ahead: 320 x 1 208 against 218 us, 384 x 1 243 against 249, 640 x 1 356 against 393, 768 x 1 413 against 426; and
+        // parts of 267 tiles (64 queries, 4 heads per group, 512 x 1) take 355 us against 330, where parts of 139 tiles (32
+        // queries, 8 heads per group) take 246 against 262.  Equal lengths with a single part went both ways (40-node
+        // trees, 480 x 1: 384 -> 360 us; 64-query chains, 448 x 1: 410 -> 447) and keep separate slices.
+        const int parts_all = std::min(std::max(1, ceil_div(ntw + nts, per_s)), kCombineRowsMaxSlots / 2);
+        const int parts = std::min(parts_all, std::max(1, kResidentWgs / units));
+        const int tiles_b[2] = {ntw, nts};
+        const int per_b = tiles_per_slice(tiles_b, 2, units);
+        const int sep_w = std::min(std::max(1, ceil_div(ntw, per_b)), cap_ws), sep_s = std::min(std::max(1, ceil_div(nts, per_b)), cap_ws);
+        const int64_t places = (int64_t)ceil_div(units * parts, kResidentWgs) * kResidentWgs;
+        if (parts == parts_all ? units * parts <= kResidentWgs
+                               : ceil_div(ntw + nts, parts) <= kJointMaxTiles && !(few_slots && 2 * parts > sep_w + sep_s) &&
+                                     (parts > 1 || (lo->scan_balanced && 20 * (int64_t)units >= 17 * places))) {
             lo->joint_parts = parts;
             pl.n_win_splits = pl.n_slc_splits = parts;
         } else {
-            const int tiles_b[2] = {ntw, nts};
-            per_w = per_s = tiles_per_slice(tiles_b, 2, units);
-            pl.n_win_splits = std::min(std::max(1, ceil_div(ntw, per_w)), cap_ws);
-            pl.n_slc_splits = std::min(std::max(1, ceil_div(nts, per_s)), cap_ws);
+            per_w = per_s = per_b;
+            pl.n_win_splits = sep_w;
+            pl.n_slc_splits = sep_s;
         }
     }
     // The streaming kernel's compressed scan of a batch of mixed lengths: slices per sequence in proportion to its length,
@@ -374,6 +391,17 @@ int make_layout(const ssv_nsa_params* p, Layout* lo) {
     lo->total = off;
     pl.workspace_bytes = (int64_t)off;
     return SSV_OK;
+}
+
+// The finer cuts take more partial-state slots; where they alone push a call past the static scratch array, it keeps the
+// plan with fewer slots, so that ssv_nsa_verify_static takes every call that some plan fits into the array.
+int make_layout(const ssv_nsa_params* p, Layout* lo) {
+    const int rc = make_layout_with(p, false, lo);
+    if (rc == SSV_OK && lo->total > (size_t)SSV_STATIC_SCRATCH_BYTES) {
+        Layout few;
+        if (make_layout_with(p, true, &few) == SSV_OK && few.total <= (size_t)SSV_STATIC_SCRATCH_BYTES) *lo = few;
+    }
+    return rc;
 }
 
 // The importance kernel of a shape: bf16 on the 32x32x16 matrix instruction, fp32 on 16x16x4; by heads-per-group class

@@ -630,3 +630,20 @@ def test_streaming_scan_work_table(dev_mod, oracle):
             out_g, sel_g = dev_g.results()
             check(case, compare(case, oracle, ref, out_g, sel_g))
     run_shared(dev_mod, oracle, cases[0], 2, scan_kernel=B.SSV_SCAN_STREAM_TABLE)
+
+
+@pytest.mark.parametrize("batch,queries,parts", [(60, 2, 1), (31, 2, 2), (21, 1, 3)])
+def test_joint_parts_of_the_selected_launch(dev_mod, oracle, batch, queries, parts):
+    """Window tiles and schedule entries cut together behind the matrix-core scan, by the parts that one round of
+    workgroups leaves a group: lengths shorter than the parts, sequences without queries or with one of two, refresh and reuse."""
+    from paper_2605_19893_amd import binding as B
+    rng = np.random.default_rng(1300 + batch)
+    lens = rng.integers(20, 1500, size=batch).tolist()
+    lens[1], lens[2] = 2600, 40
+    nq = rng.integers(1, queries + 1, size=batch).tolist()
+    nq[batch // 2] = 0
+    case = si.make_case(f"joint_b{batch}_t{queries}", "bf16", batch, queries, 16, 8, 64, 64, si.STD_NSA, lens, 1301 + batch, rho=0.4,
+                        n_query=nq, poison_pad=True)
+    dev, ref, out, sel = run_refresh(dev_mod, oracle, case, scan_kernel=B.SSV_SCAN_MATRIX)
+    assert dev.plan.scan_matrix == 1 and (dev.plan.n_win_splits, dev.plan.n_slc_splits) == (parts, parts)
+    run_reuse(dev_mod, oracle, case, sel, dev=dev)
