@@ -34,7 +34,8 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Planning constants (measured choices; none is read from the environment).
 constexpr int kResidentWgs = 256 * 2;        // workgroups one round holds: LDS and registers allow two per CU
-constexpr int kMinTilesPerSlice = 2;
+constexpr int kMinTilesPerSlice = 1;         // one tile per workgroup only where all tiles of the launch fit one workgroup per CU (a floor of
+                                             // two: 1 to 4 queries over 1K to 8K tokens, bf16 30 to 34 us against 27 to 32, fp32 37 against 31)
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
 constexpr int kJointMaxTiles = 160;          // window tiles and schedule entries that one workgroup of the joint launch takes, at most
@@ -76,7 +77,7 @@ void stream_tile_lds(bool bf16, int d_k, int d_v, size_t* lds_k, size_t* lds_vt)
     *lds_vt = bf16 ? (size_t)kTile * (d_v * 2 + 32) : (size_t)d_v * (kTile * 4 + 16);
 }
 
-// few_slots: no branch gets more slots for being cut together with the other
+// few_slots: no slice is shorter than two tiles and no branch gets more slots for being cut together with the other
 int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     if (!p) return SSV_EINVAL;
     if (p->B < 1 || p->T < 1 || p->H < 1 || p->H_kv < 1 || p->d_k < 1 || p->d_v < 1) return SSV_EINVAL;
@@ -193,7 +194,7 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     pl.max_sched_entries = pl.C * p->n_sel;
     // selected tiles, at most; with one shared index set per group the schedule is a single set
     const int nts = shared ? ceil_div(pl.C, pl.share_group) * p->n_sel : pl.max_sched_entries;
-    pl.min_tiles_per_split = kMinTilesPerSlice;
+    pl.min_tiles_per_split = few_slots ? 2 : kMinTilesPerSlice;
     const int mt = pl.min_tiles_per_split;
     const int long_slice = p->max_slice_tiles ? p->max_slice_tiles : kLongSliceTiles;
     // Tiles per slice.  If one round of resident workgroups can take the launch with slices of at most long_slice
