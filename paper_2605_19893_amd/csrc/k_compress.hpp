@@ -27,7 +27,12 @@ struct CompressArgs {
 
 __device__ __forceinline__ int complete_cmp_rows(int L, int l, int d) { return L < l ? 0 : (L - l) / d + 1; }
 
-template <bool BF16>
+// STREAM: raw rows are loaded and compressed rows stored with the non-temporal hint.  A build reads far more than the
+// last-level cache holds and every row once, so lines that are kept only displace others: 16 sequences of 64K tokens
+// (2.7 GB read, 0.17 written) 536 -> 504 us, 5.3 -> 5.65 TB/s; with 64 chunks per workgroup and ordinary stores 536.  Where
+// the rows read fit the cache they may still be there from the verification that accepted them: 32 sequences gaining
+// up to 512 tokens take 10.2 us with ordinary loads and 10.8 with the hint.
+template <bool BF16, bool STREAM>
 __global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
     constexpr int EPG = BF16 ? 8 : 4;           // elements per 16-byte group
     extern __shared__ __align__(16) char smem[];
@@ -51,6 +56,10 @@ __global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
     const char* src = is_v ? a.v + b * a.v_s[0] + h * a.v_s[1] : a.k + b * a.k_s[0] + h * a.k_s[1];
     const int n_rows = r1 - r0, n_chunks = n_rows + a.ratio - 1;
 
+    auto load_row = [](const char* row) {
+        if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row));
+        else return *reinterpret_cast<const u32x4*>(row);
+    };
     // chunk sums: chunk x of the run covers slots [(r0 + x) d, (r0 + x + 1) d), all below L_after
     for (int task = tid; task < n_chunks * groups; task += kThreads) {
         const int x = task / groups, cg = task - x * groups;
@@ -73,12 +82,12 @@ __global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
         if (a.d == 16) {        // the standard stride: all sixteen row loads in flight before the first add
             u32x4 raw[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) raw[r] = *reinterpret_cast<const u32x4*>(p + r * src_row);
+            for (int r = 0; r < 16; ++r) raw[r] = load_row(p + r * src_row);
 #pragma unroll
             for (int r = 0; r < 16; ++r) add_row(raw[r]);
         } else {
 #pragma unroll 4
-            for (int r = 0; r < a.d; ++r) add_row(*reinterpret_cast<const u32x4*>(p + r * src_row));
+            for (int r = 0; r < a.d; ++r) add_row(load_row(p + r * src_row));
         }
 #pragma unroll
         for (int e = 0; e < EPG; e += 4)
@@ -108,7 +117,9 @@ __global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) packed[e] = __float_as_uint(acc[e] * a.inv_l);
         }
-        *reinterpret_cast<u32x4*>(dst + (int64_t)(r0 + c) * dst_row + cg * 16) = packed;
+        u32x4* const to = reinterpret_cast<u32x4*>(dst + (int64_t)(r0 + c) * dst_row + cg * 16);
+        if constexpr (STREAM) __builtin_nontemporal_store(packed, to);
+        else *to = packed;
     }
 }
 

@@ -96,6 +96,19 @@ def test_full_build_fp32_and_other_ratios(torch_mod):
     run_compress(torch_mod, "bf16", 1, 1, 128, 128, 64, 8, 600, None, [600], 5)
 
 
+@pytest.mark.parametrize("dtype,H_kv,d_k,d_v,l,d", [("bf16", 4, 192, 128, 32, 16), ("f32", 4, 64, 64, 32, 16), ("bf16", 2, 128, 128, 64, 8)])
+def test_builds_that_may_outgrow_the_cache(torch_mod, dtype, H_kv, d_k, d_v, l, d):
+    """The streaming form (chosen by the rows the caller allows for: non-temporal loads and stores): run
+    lengths just below, at and above a workgroup's rows, none at all, and an update that starts inside a run."""
+    rows = 33 - l // d
+    allowed = (300 << 20) // (4 * H_kv * d * (d_k + d_v) * (2 if dtype == "bf16" else 4))
+    tokens = lambda n: (n - 1) * d + l
+    run_compress(torch_mod, dtype, 4, H_kv, d_k, d_v, l, d, tokens(2 * rows + 1) + 5, None,
+                 [tokens(rows - 1), tokens(rows), tokens(rows + 1), tokens(2 * rows + 1) + 3], 21, max_new_rows=allowed)
+    run_compress(torch_mod, dtype, 4, H_kv, d_k, d_v, l, d, tokens(2 * rows + 1), [l - 1, tokens(3), 0, tokens(rows)],
+                 [l, tokens(rows + 4), l - 1, tokens(2 * rows + 1)], 22, max_new_rows=allowed)
+
+
 def test_incremental_updates_and_deferred_commit(torch_mod):
     """Verification rounds: 0..16 accepted tokens at a time; only rows whose tokens are all committed appear."""
     before = [4096, 1000, 31, 47, 640]
