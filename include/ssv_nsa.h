@@ -147,8 +147,8 @@ typedef struct ssv_nsa_plan {
     int32_t rows_per_wg;      /* C * H_g */
     int32_t n_cmp_chunks;     /* workgroups splitting the compressed scan of one group */
     int32_t tiles_per_chunk;  /* 64-row tiles of k_cmp/v_cmp per such workgroup */
-    int32_t n_win_splits;     /* workgroups splitting the window tiles of one group */
-    int32_t n_slc_splits;     /* workgroups splitting the merged selected-block schedule of one group */
+    int32_t n_win_splits;     /* slices of the window tiles of one group (a workgroup each, or one that walks several) */
+    int32_t n_slc_splits;     /* slices of the merged selected-block schedule of one group (likewise) */
     int32_t min_tiles_per_split;
     int32_t n_slots;          /* partial softmax states per output row = sum of the three above */
     int32_t max_sched_entries;/* capacity of the merged schedule of one group */

@@ -34,6 +34,7 @@ struct StreamArgs {
     const int32_t* cmp_table; // launches with the compressed scan: its work table (below), or null
     int cmp_items_max;       // capacity of that table in items
     int joint;               // <WIN|SLC> launch: > 0 = parts per group over window tiles and schedule entries together (below)
+    int walk;                // <WIN|SLC> launch: != 0: one workgroup per group walks the group's slices (below)
     int n_wg;                // real workgroups (the grid is padded to a multiple of 8)
     int max_sched, bitmap_words;
     int64_t rows_total;
@@ -103,6 +104,10 @@ __device__ __forceinline__ void even_slice(int n, int parts, int min_items, int 
 // [n_cmp_chunks, + P) and [n_cmp_chunks + P, + P)); the state of a branch its part does not touch is marked empty.
 // Separate slices per branch leave the window's workgroup (9 tiles at w = 512) idle while the schedule's
 // (up to 32 tiles each) run on.
+//
+// Walking slices (the <WIN|SLC> launch, walk != 0): the branches are cut into slices as always, each with a slot of its
+// own, but one workgroup takes all slices of a group one after the other: the group starts up and builds its schedule once
+// instead of once per slice.  Slices, states and results are those of the launch with a workgroup per slice, bit for bit.
 constexpr int kRolesCmp = 1, kRolesWin = 2, kRolesCmpWin = 3, kRolesSlc = 4, kRolesWinSlc = 6, kRolesAll = 7;
 
 // Two workgroups per CU (the LDS of the full-size shapes allows no more), stated to the compiler as exactly two
@@ -166,15 +171,15 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
         g = bg % a.H_kv;
     }
 
-    const bool joint = ROLES == kRolesWinSlc && a.joint > 0;    // (uniform for the launch)
+    const bool joint = ROLES == kRolesWinSlc && a.joint > 0, walk = ROLES == kRolesWinSlc && a.walk != 0;    // (uniform for the launch)
     int role, part;
-    if (joint) { role = ROLE_SLC; part = slot - a.slot_lo; }     // (the role of the first segment is set below)
+    if (joint || walk) { role = ROLE_SLC; part = slot - a.slot_lo; }     // (the role of every segment is set below)
     else if (slot < a.n_cmp_chunks) { role = ROLE_CMP; part = slot; }
     else if (slot < a.n_cmp_chunks + a.n_win_splits) { role = ROLE_WIN; part = slot - a.n_cmp_chunks; }
     else { role = ROLE_SLC; part = slot - a.n_cmp_chunks - a.n_win_splits; }
     const bool r_cmp = (ROLES & 1) && role == ROLE_CMP;
     bool r_win = (ROLES & 2) && role == ROLE_WIN;
-    bool r_slc = (ROLES & 4) && role == ROLE_SLC;      // joint: true up to the schedule's construction, then per segment
+    bool r_slc = (ROLES & 4) && role == ROLE_SLC;      // joint, walk: true up to the schedule's construction, then per segment
 
     // ---- query fragments (B operand of S^T = K Q^T), kept in registers for the whole slice.  Their addresses need
     //      nothing from the sequence's metadata, so the loads go first and overlap the latency of everything below
@@ -247,7 +252,7 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
 
     // ---- tile range of this workgroup
     int t0 = 0, t1 = 0;           // CMP / WIN: tile indices; SLC: schedule entries
-    int jw0 = 0, jw1 = 0, js0 = 0, js1 = 0;      // joint slicing: both ranges
+    int jw0 = 0, jw1 = 0, js0 = 0, js1 = 0;      // joint slicing: both ranges; walk: the group's window tiles [jw0, jw1), entries [0, js1)
     if (nq_grp > 0) {
         if (r_cmp) {
             int cm = 0;
@@ -304,15 +309,15 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
             }
             __syncthreads();
             const int len = s_scalar[0];
-            if (!joint) even_slice(len, a.n_slc_splits, a.min_tiles, part, t0, t1);
+            if (!joint && !walk) even_slice(len, a.n_slc_splits, a.min_tiles, part, t0, t1);
             else {
                 // this part of [window tiles | schedule entries]: its window tiles [jw0, jw1), its entries [js0, js1)
                 int dmin = 1 << 30;
                 for (int j = 0; j < nq_grp; ++j) dmin = min(dmin, s_depth[qg * a.C + j]);
                 const int wlo = max(0, L + dmin - a.w + 1) / kTile;
                 const int nw = (n_slots_kv + kTile - 1) / kTile - wlo;
-                int lo, hi;
-                even_slice(nw + len, a.joint, a.min_tiles, part, lo, hi);
+                int lo = 0, hi = nw + len;
+                if (joint) even_slice(nw + len, a.joint, a.min_tiles, part, lo, hi);
                 jw0 = wlo + min(lo, nw);
                 jw1 = wlo + min(hi, nw);
                 js0 = max(lo, nw) - nw;
@@ -591,17 +596,26 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
             }
         }
     };
-    // One segment; joint slicing: the part's window tiles, then its schedule entries, a state for each.
+    // One segment; joint slicing: the part's window tiles, then its schedule entries, a state for each; walk: all
+    // slices of the group, a state for each.
     int out_slot = slot;
-    for (int seg = 0; seg < (joint ? 2 : 1); ++seg) {
+    const int n_seg = joint ? 2 : (walk ? a.n_win_splits + a.n_slc_splits : 1);
+    for (int seg = 0; seg < n_seg; ++seg) {
         if (joint) {
             r_win = seg == 0;
             r_slc = seg == 1;
             t0 = seg == 0 ? jw0 : js0;
             t1 = seg == 0 ? jw1 : js1;
             out_slot = a.n_cmp_chunks + seg * a.joint + part;
-            if (seg) __syncthreads();     // every wave has finished reading the window's last tile
+        } else if (walk) {
+            r_win = seg < a.n_win_splits;
+            r_slc = !r_win;
+            if (r_win) even_slice(jw1 - jw0, a.n_win_splits, a.min_tiles, seg, t0, t1);
+            else even_slice(js1, a.n_slc_splits, a.min_tiles, seg - a.n_win_splits, t0, t1);
+            if (r_win) { t0 += jw0; t1 += jw0; }
+            out_slot = a.n_cmp_chunks + seg;
         }
+        if (seg) __syncthreads();     // every wave has finished reading the last tile of the segment before
 #pragma unroll
         for (int t = 0; t < NRT; ++t) {
             mrun[t] = -INFINITY;

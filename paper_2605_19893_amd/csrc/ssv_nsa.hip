@@ -38,7 +38,7 @@ constexpr int kMinTilesPerSlice = 1;         // one tile per workgroup only wher
                                              // two: 1 to 4 queries over 1K to 8K tokens, bf16 30 to 34 us against 27 to 32, fp32 37 against 31)
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
-constexpr int kJointMaxTiles = 160;          // window tiles and schedule entries that one workgroup of the joint launch takes, at most
+constexpr int kWalkMaxTiles = 160;           // window tiles and schedule entries of a group whose slices one workgroup walks, at most
 constexpr int kImportanceWgs = 512;          // one round of the importance pass (more, shorter workgroups measured slower)
 constexpr int kTopnInSlcMaxWgs = 256;        // SSV_TOPN_AUTO: select inside the selected-branch launch up to this many workgroups
                                              // (twice as many when a wavefront has one query to select for)
@@ -62,6 +62,7 @@ struct Layout {
     int cmp_items_max;           // > 0: the streaming kernel's compressed scan takes its slices from a work table (k_work_table)
     bool table_kernel;           // the call starts with k_work_table
     int joint_parts;             // > 0: the <WIN|SLC> launch cuts window tiles and schedule entries of a group together
+    bool walk;                   // that launch has one workgroup per group, which walks the slices of both branches
     int imp_items_max;           // > 0: the importance pass takes its slices from the work table the balanced scan writes
     int imp_C, imp_n_qg, n_imp_chunks, imp_rw;   // importance pass: routed queries per workgroup, such workgroups per sequence, slices, blocks of 64 rows per workgroup
     int nc_pitch, max_blocks, bitmap_words, max_sched;
@@ -259,35 +260,34 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     pl.n_win_splits = std::min(std::max(1, ceil_div(ntw, per_w)), cap_ws);
     pl.n_slc_splits = std::min(std::max(1, ceil_div(nts, per_s)), cap_ws);
     lo->joint_parts = 0;
+    lo->walk = false;
     if (lo->scan32) {
-        // The parts of a group are cut over window tiles and schedule entries together, and every part owns a window slot and
-        // a selected slot (the one its tiles do not reach stays empty): no workgroup sits idle behind the window's few tiles,
-        // a group starts up and writes its states as few times as possible, and with one round the selection runs inside
-        // the launch.  As many parts as one round of resident workgroups takes; where that is fewer than the
-        // slice length asks for, parts hold at most kJointMaxTiles tiles, and a single part per group is taken in batches of mixed lengths only, where the rounds,
-        // last one included, are 85 % full: nothing evens out workgroups this long.
-        // Whole calls against separate slices per branch (refresh, 4K..128K tokens, 16 queries; groups x parts of 512 places):
-        // 192 x 2 162 -> 154 us, 256 x 2 188 -> 176, 448 x 1 270 -> 261, 512 x 1 295 -> 283, 1024 x 1 533 -> 519;
-        // 40-node trees over 64K: 240 x 2 205 -> 177.  Beyond the line separate slices stay
-        // ahead: 320 x 1 208 against 218 us, 384 x 1 243 against 249, 640 x 1 356 against 393, 768 x 1 413 against 426; and
-        // parts of 267 tiles (64 queries, 4 heads per group, 512 x 1) take 355 us against 330, where parts of 139 tiles (32
-        // queries, 8 heads per group) take 246 against 262.  Equal lengths with a single part went both ways (40-node
-        // trees, 480 x 1: 384 -> 360 us; 64-query chains, 448 x 1: 410 -> 447) and keep separate slices.
+        // Joint parts: the window tiles and the schedule entries of a group are cut together, and every part owns a window slot
+        // and a selected slot (the one its tiles do not reach stays empty): no workgroup sits idle behind the window's few
+        // tiles, and with one round the selection runs inside the launch.  As many parts as one round of resident workgroups
+        // takes, but only where they cut the schedule no coarser than slices of its own would: every slice has one
+        // probability that is exactly 1 in bf16, and with fewer slices the result is further off (one part in place of
+        // two slices, 32 sequences of 16 queries: 2.148e-3 -> 2.156e-3 of the 64-bit result, the same on every input).
+        // Otherwise each branch keeps slices of its own.  In batches of mixed lengths one workgroup walks all slices of a
+        // group where the rounds of such workgroups, last one included, are 85 % full and a group has at most kWalkMaxTiles
+        // tiles: one start-up and one schedule per group instead of one per slice, the same slices and results.
+        // Whole calls against a workgroup per slice (refresh, 4K..128K tokens, 16 queries; groups x parts of 512 places):
+        // 192 x 2 141 -> 130 us, 256 x 2 159 -> 138; walked: 512 groups 257 -> 245, 1024 groups 403 -> 392; 40-node trees
+        // over 64K: 240 x 2 196 -> 173.
         const int parts_all = std::min(std::max(1, ceil_div(ntw + nts, per_s)), kCombineRowsMaxSlots / 2);
         const int parts = std::min(parts_all, std::max(1, kResidentWgs / units));
         const int tiles_b[2] = {ntw, nts};
         const int per_b = tiles_per_slice(tiles_b, 2, units);
         const int sep_w = std::min(std::max(1, ceil_div(ntw, per_b)), cap_ws), sep_s = std::min(std::max(1, ceil_div(nts, per_b)), cap_ws);
-        const int64_t places = (int64_t)ceil_div(units * parts, kResidentWgs) * kResidentWgs;
-        if (parts == parts_all ? units * parts <= kResidentWgs
-                               : ceil_div(ntw + nts, parts) <= kJointMaxTiles && !(few_slots && 2 * parts > sep_w + sep_s) &&
-                                     (parts > 1 || (lo->scan_balanced && 20 * (int64_t)units >= 17 * places))) {
+        if (units * parts <= kResidentWgs && (parts == parts_all || (parts > 1 && parts >= sep_s && !(few_slots && 2 * parts > sep_w + sep_s)))) {
             lo->joint_parts = parts;
             pl.n_win_splits = pl.n_slc_splits = parts;
         } else {
             per_w = per_s = per_b;
             pl.n_win_splits = sep_w;
             pl.n_slc_splits = sep_s;
+            const int64_t places = (int64_t)ceil_div(units, kResidentWgs) * kResidentWgs;
+            lo->walk = lo->scan_balanced && !p->max_slice_tiles && ntw + nts <= kWalkMaxTiles && 20 * (int64_t)units >= 17 * places;
         }
     }
     // The streaming kernel's compressed scan of a batch of mixed lengths: slices per sequence in proportion to its length,
@@ -367,7 +367,7 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     // separate launch once the chip is full.
     const bool refresh = p->mode != SSV_REUSE;
     const bool fits = fused_topn_lds_bytes(max_blocks, pl.C, p->n_sel) <= lo->lds_k + lo->lds_vt;
-    const int n_wg_b = units * (lo->joint_parts ? lo->joint_parts : pl.n_slc_splits + (lo->scan32 ? pl.n_win_splits : 0));
+    const int n_wg_b = units * (lo->joint_parts ? lo->joint_parts : lo->walk ? 1 : pl.n_slc_splits + (lo->scan32 ? pl.n_win_splits : 0));
     pl.topn_in_slc = refresh && !unfused && fits &&
                      (p->topn_home == SSV_TOPN_IN_SLC || (p->topn_home == SSV_TOPN_AUTO && n_wg_b <= (pl.C <= 4 ? 2 : 1) * kTopnInSlcMaxWgs));
     pl.n_imp_chunks = refresh ? lo->n_imp_chunks : 0;
@@ -546,7 +546,8 @@ int launch_all(const void* q, const void* k, const void* v, const void* kc, cons
         if (tabled) sa.n_wg = (lo.cmp_items_max + p->B * (slot_cnt - pl.n_cmp_chunks)) * p->H_kv * n_qg;
         // A launch of several rounds of workgroups gains nothing from cutting a short sequence into slices of one
         // or two tiles: every slice pays the start-up of a workgroup and leaves a partial state to merge.
-        sa.min_tiles = sa.n_wg > kResidentWgs ? kMinTilesMultiRound : 1;
+        // (walked slices are those of the launch with a workgroup for each, which has several rounds)
+        sa.min_tiles = sa.n_wg > kResidentWgs || lo.walk ? kMinTilesMultiRound : 1;
         const int grid = tabled ? ceil_div(sa.n_wg, 8 * n_qg) * 8 * n_qg : ceil_div(sa.n_wg, 8) * 8;
         if (tm.begin(K)) return -1;
         if (tabled) {
@@ -700,8 +701,9 @@ int launch_all(const void* q, const void* k, const void* v, const void* kc, cons
         if (launch_scan32()) return SSV_ELAUNCH;
         if (p->mode != SSV_REUSE && launch_routing()) return SSV_ELAUNCH;
         sa.joint = lo.joint_parts;
-        if (launch_stream(SSV_K_STREAM_B, kRolesWinSlc, pl.n_cmp_chunks, lo.joint_parts ? lo.joint_parts : pl.n_win_splits + pl.n_slc_splits, pl.C,
-                          pl.n_qg))
+        sa.walk = lo.walk;
+        const int n_b = lo.joint_parts ? lo.joint_parts : lo.walk ? 1 : pl.n_win_splits + pl.n_slc_splits;
+        if (launch_stream(SSV_K_STREAM_B, kRolesWinSlc, pl.n_cmp_chunks, n_b, pl.C, pl.n_qg))
             return SSV_ELAUNCH;
     } else if (lo.one_launch) {
         if (launch_stream(SSV_K_STREAM_A, kRolesAll, 0, pl.n_slots, pl.C, pl.n_qg)) return SSV_ELAUNCH;

@@ -632,18 +632,49 @@ def test_streaming_scan_work_table(dev_mod, oracle):
     run_shared(dev_mod, oracle, cases[0], 2, scan_kernel=B.SSV_SCAN_STREAM_TABLE)
 
 
-@pytest.mark.parametrize("batch,queries,parts", [(60, 2, 1), (31, 2, 2), (21, 1, 3)])
-def test_joint_parts_of_the_selected_launch(dev_mod, oracle, batch, queries, parts):
-    """Window tiles and schedule entries cut together behind the matrix-core scan, by the parts that one round of
-    workgroups leaves a group: lengths shorter than the parts, sequences without queries or with one of two, refresh and reuse."""
-    from paper_2605_19893_amd import binding as B
-    rng = np.random.default_rng(1300 + batch)
-    lens = rng.integers(20, 1500, size=batch).tolist()
-    lens[1], lens[2] = 2600, 40
+def _mixed_batch(name, batch, queries, seed, heads=16, kv_heads=8, d=64, longest=2600, parents=None):
+    """Lengths shorter than a slice and a few tiles long, sequences without queries or with one of several."""
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(20, longest * 3 // 5, size=batch).tolist()
+    lens[1], lens[2] = longest, 40
     nq = rng.integers(1, queries + 1, size=batch).tolist()
-    nq[batch // 2] = 0
-    case = si.make_case(f"joint_b{batch}_t{queries}", "bf16", batch, queries, 16, 8, 64, 64, si.STD_NSA, lens, 1301 + batch, rho=0.4,
-                        n_query=nq, poison_pad=True)
+    nq[1], nq[batch // 2] = queries, 0
+    return si.make_case(f"{name}_b{batch}_t{queries}", "bf16", batch, queries, heads, kv_heads, d, d, si.STD_NSA, lens, seed + 1, rho=0.4,
+                        n_query=nq, parents=parents, poison_pad=True)
+
+
+@pytest.mark.parametrize("batch,queries,parts,all_parts", [(31, 2, 2, 2), (21, 1, 3, 3), (22, 4, 2, 3)])
+def test_joint_parts_of_the_selected_launch(dev_mod, oracle, batch, queries, parts, all_parts):
+    """Window tiles and schedule entries cut together behind the matrix-core scan, refresh and reuse: as many parts as the
+    slice length asks for, and the fewer that one round of workgroups leaves a group."""
+    from paper_2605_19893_amd import binding as B
+    case = _mixed_batch("joint", batch, queries, 1300 + batch, d=128)
     dev, ref, out, sel = run_refresh(dev_mod, oracle, case, scan_kernel=B.SSV_SCAN_MATRIX)
-    assert dev.plan.scan_matrix == 1 and (dev.plan.n_win_splits, dev.plan.n_slc_splits) == (parts, parts)
+    pl = dev.plan
+    assert pl.scan_matrix == 1 and (pl.n_win_splits, pl.n_slc_splits) == (parts, parts)
+    assert (batch * 8 * pl.n_qg * all_parts > 512) == (parts < all_parts)
     run_reuse(dev_mod, oracle, case, sel, dev=dev)
+
+
+# one round with the selection inside, a slice or two of the schedule; a tree of six with a launch of its own for the
+# selection; nearly two rounds
+@pytest.mark.parametrize("batch,queries,tree,n_slc,topn_in_slc", [(30, 2, False, 1, 1), (31, 4, False, 2, 1), (31, 6, True, 3, 0),
+                                                                 (63, 4, False, 2, 0)])
+def test_walked_slices_are_the_slices(dev_mod, oracle, batch, queries, tree, n_slc, topn_in_slc):
+    """One workgroup per group walks the group's slices: the outputs are those of a workgroup per slice, bit for bit (the
+    bound of 32 tiles on a slice is the automatic one, stated: it keeps the slices and turns the walk off)."""
+    from paper_2605_19893_amd import binding as B
+    case = _mixed_batch("walk", batch, queries, 1400 + batch + queries, heads=32, kv_heads=16, d=128, longest=1300,
+                        parents=si.tree_parents((2, 2), "bfs") if tree else None)
+    dev, ref, out, sel = run_refresh(dev_mod, oracle, case, scan_kernel=B.SSV_SCAN_MATRIX)
+    each = dev_mod.DeviceCase(case, scan_kernel=B.SSV_SCAN_MATRIX, max_slice_tiles=32)
+    slots = lambda p: (p.scan_matrix, p.n_cmp_chunks, p.n_win_splits, p.n_slc_splits, p.n_slots)
+    assert slots(dev.plan) == slots(each.plan) and (dev.plan.n_win_splits, dev.plan.n_slc_splits) == (1, n_slc)
+    assert (dev.plan.topn_in_slc, each.plan.topn_in_slc) == (topn_in_slc, 0)
+    each.run()
+    out_each, sel_each = each.results()
+    assert np.array_equal(sel, sel_each) and np.array_equal(out, out_each)
+    out_reuse = run_reuse(dev_mod, oracle, case, sel, dev=dev)
+    each.set_mode(B.SSV_REUSE)
+    each.run()
+    assert np.array_equal(out_reuse, each.results()[0])
