@@ -131,7 +131,9 @@ typedef struct ssv_nsa_params {
                              scan_group_size must be 0 or 1 there) */
     int32_t topn_home;    /* SSV_TOPN_AUTO, SSV_TOPN_SEPARATE or SSV_TOPN_IN_SLC; never changes the result */
     int32_t max_slice_tiles; /* upper bound on the 64-row tiles one workgroup streams when a launch needs several
-                             rounds of workgroups (2..64; 0 = automatic: 32); never changes the result */
+                             rounds of workgroups (2..64; 0 = automatic: 32, and more where the window and selected
+                             tiles of a group fill one round of workgroups, or nearly full rounds, with fewer, longer
+                             parts); never changes the result beyond rounding */
     int32_t imp_rows;     /* rows (routed queries x heads of a group) per workgroup in the importance pass of a refresh
                              call: 64, 128 or 256; 0 = automatic (more than 64 where a KV head has that many rows and
                              the pass runs for several tiles per workgroup); never changes the result */

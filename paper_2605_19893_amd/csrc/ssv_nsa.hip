@@ -279,7 +279,9 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         const int tiles_b[2] = {ntw, nts};
         const int per_b = tiles_per_slice(tiles_b, 2, units);
         const int sep_w = std::min(std::max(1, ceil_div(ntw, per_b)), cap_ws), sep_s = std::min(std::max(1, ceil_div(nts, per_b)), cap_ws);
-        if (units * parts <= kResidentWgs && (parts == parts_all || (parts > 1 && parts >= sep_s && !(few_slots && 2 * parts > sep_w + sep_s)))) {
+        // (fewer parts than the slice length asks for are longer ones: not past a bound that the caller gave)
+        const bool fewer = parts > 1 && parts >= sep_s && (!p->max_slice_tiles || ceil_div(ntw + nts, parts) <= p->max_slice_tiles);
+        if (units * parts <= kResidentWgs && (parts == parts_all || (fewer && !(few_slots && 2 * parts > sep_w + sep_s)))) {
             lo->joint_parts = parts;
             pl.n_win_splits = pl.n_slc_splits = parts;
         } else {

@@ -229,6 +229,22 @@ def test_plan_reflects_the_execution_choices():
     assert un.workspace_bytes >= 3 * rows * 128 * 2 + un.n_slots * rows * 130 * 4
 
 
+@pytest.mark.parametrize("B_,T,avg", [(32, 16, 40000), (64, 16, 40000), (16, 16, 0), (12, 16, 40000), (6, 40, 0)])
+def test_explicit_slice_bound_holds_behind_the_matrix_core_scan(B_, T, avg):
+    """An explicit max_slice_tiles bounds the window and selected tiles of one workgroup: launches that would otherwise take
+    fewer, longer parts keep the slices the bound asks for."""
+    tiles = 16 * 4 + (512 + T) // 64 + 2          # schedule entries of four queries and window tiles, at most
+    for bound in (2, 5, 8, 12, 24, 32):
+        pl = B.ssv_nsa_plan_query(std_params(B=B_, T=T, max_seq_len=131072, max_n_cmp=8191, avg_seq_len=avg, max_slice_tiles=bound))
+        assert pl.scan_matrix == 1 and pl.max_sched_entries == 64
+        groups = B_ * 4 * pl.n_qg
+        if pl.n_win_splits == pl.n_slc_splits and groups * pl.n_win_splits <= 512:      # cut together in one round
+            assert -(-tiles // pl.n_slc_splits) <= bound, (bound, pl.n_slc_splits)
+        else:
+            assert pl.n_slc_splits >= min(32, -(-64 // bound)), (bound, pl.n_slc_splits)
+            assert pl.n_win_splits >= min(32, -(-(tiles - 64) // bound)), (bound, pl.n_win_splits)
+
+
 def test_plan_workspace_and_verify_agree():
     """One set of checks serves the three entry points: whatever the plan query accepts, the workspace query sizes
     and verify accepts (up to its pointer checks), and the reverse."""
