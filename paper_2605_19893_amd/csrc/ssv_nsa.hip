@@ -38,7 +38,7 @@ constexpr int kMinTilesPerSlice = 1;         // one tile per workgroup only wher
                                              // two: 1 to 4 queries over 1K to 8K tokens, bf16 30 to 34 us against 27 to 32, fp32 37 against 31)
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
-constexpr int kWalkMaxTiles = 160;           // window tiles and schedule entries of a group whose slices one workgroup walks, at most
+constexpr int kWalkIdleTiles = 8;            // one workgroup walks a group's slices where the last round's empty places cost at most this many tile steps
 constexpr int kImportanceWgs = 512;          // one round of the importance pass (more, shorter workgroups measured slower)
 constexpr int kTopnInSlcMaxWgs = 256;        // SSV_TOPN_AUTO: select inside the selected-branch launch up to this many workgroups
                                              // (twice as many when a wavefront has one query to select for)
@@ -268,19 +268,31 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         // takes, but only where they cut the schedule no coarser than slices of its own would: every slice has one
         // probability that is exactly 1 in bf16, and with fewer slices the result is further off (one part in place of
         // two slices, 32 sequences of 16 queries: 2.148e-3 -> 2.156e-3 of the 64-bit result, the same on every input).
-        // Otherwise each branch keeps slices of its own.  In batches of mixed lengths one workgroup walks all slices of a
-        // group where the rounds of such workgroups, last one included, are 85 % full and a group has at most kWalkMaxTiles
-        // tiles: one start-up and one schedule per group instead of one per slice, the same slices and results.
-        // Whole calls against a workgroup per slice (refresh, 4K..128K tokens, 16 queries; groups x parts of 512 places):
-        // 192 x 2 141 -> 130 us, 256 x 2 159 -> 138; walked: 512 groups 257 -> 245, 1024 groups 403 -> 392; 40-node trees
-        // over 64K: 240 x 2 196 -> 173.
+        // Whole calls against a workgroup per slice (16 queries, groups x parts of 512 places, refresh and reuse): 192 x 2
+        // 141 -> 130 and 115 -> 106 us, 256 x 2 159 -> 138 and 128 -> 110; 176 x 2 157 -> 156 and 121 -> 116; 128 x 4 (32
+        // queries, 8 heads per group) 136 -> 125 and 98 -> 87; 40-node trees 240 x 2 196 -> 173 and 147 -> 126.
+        // Otherwise each branch keeps slices of its own, and in batches of mixed lengths (the caller's average below the
+        // maximum) one workgroup walks all slices of a group where one per group nearly fills its rounds: one start-up and
+        // one schedule per group instead of one per slice, the same slices and results.  What it costs is the empty places of the last round: the launch is idle places x tiles of a group / 512
+        // tile steps longer than an even spread, and workgroups this long leave nothing to even that out.  The line of
+        // kWalkIdleTiles lies between (calls in us, a workgroup per slice -> walked)
+        // 464 groups of 75 tiles (7.0: 217 -> 209), 480 (4.7: 231 -> 217), 992 (4.7: 396 -> 390), 1504 (4.7: 486 -> 478), 496 of 139
+        // tiles (4.3: 286 -> 280) and full rounds (512: 257 -> 245, 1024: 403 -> 392, 512 of 139 tiles 281 -> 276, 1024 of
+        // 267 tiles 559 -> 512) on one side and 448 (9.4: 236 -> 234 refresh, 193 -> 196 reuse), 960 (9.4: 387 -> 387), 928
+        // (14: 372 -> 376), 480 of 139 tiles (8.7: 291 -> 288 and 253 -> 254; 8 heads per group 224 -> 227), 896 (19: 354 ->
+        // 362), 640 (56: 273 -> 314) on the other.
+        // Lengths do not enter into it: equal ones gain as much (480 groups of 75 tiles 266 -> 255, 512 351 -> 339) and lose as
+        // much (640: 331 -> 371); they keep a workgroup per slice, the plan they have had.
+        // Both need launches of two resident workgroups per CU.  At d_k = 64 the kernel takes 157 registers, three fit, and
+        // 512 is no round: 240 x 2 67 -> 71 us, 480 groups of 75 tiles 105 -> 116, of 139 tiles 120 -> 143.
         const int parts_all = std::min(std::max(1, ceil_div(ntw + nts, per_s)), kCombineRowsMaxSlots / 2);
         const int parts = std::min(parts_all, std::max(1, kResidentWgs / units));
         const int tiles_b[2] = {ntw, nts};
         const int per_b = tiles_per_slice(tiles_b, 2, units);
         const int sep_w = std::min(std::max(1, ceil_div(ntw, per_b)), cap_ws), sep_s = std::min(std::max(1, ceil_div(nts, per_b)), cap_ws);
         // (fewer parts than the slice length asks for are longer ones: not past a bound that the caller gave)
-        const bool fewer = parts > 1 && parts >= sep_s && (!p->max_slice_tiles || ceil_div(ntw + nts, parts) <= p->max_slice_tiles);
+        const bool two_per_cu = p->d_k > 64;
+        const bool fewer = two_per_cu && parts > 1 && parts >= sep_s && (!p->max_slice_tiles || ceil_div(ntw + nts, parts) <= p->max_slice_tiles);
         if (units * parts <= kResidentWgs && (parts == parts_all || (fewer && !(few_slots && 2 * parts > sep_w + sep_s)))) {
             lo->joint_parts = parts;
             pl.n_win_splits = pl.n_slc_splits = parts;
@@ -288,8 +300,8 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
             per_w = per_s = per_b;
             pl.n_win_splits = sep_w;
             pl.n_slc_splits = sep_s;
-            const int64_t places = (int64_t)ceil_div(units, kResidentWgs) * kResidentWgs;
-            lo->walk = lo->scan_balanced && !p->max_slice_tiles && ntw + nts <= kWalkMaxTiles && 20 * (int64_t)units >= 17 * places;
+            const int64_t idle = (int64_t)ceil_div(units, kResidentWgs) * kResidentWgs - units;
+            lo->walk = lo->scan_balanced && two_per_cu && !p->max_slice_tiles && idle * (ntw + nts) <= (int64_t)kWalkIdleTiles * kResidentWgs;
         }
     }
     // The streaming kernel's compressed scan of a batch of mixed lengths: slices per sequence in proportion to its length,
