@@ -34,8 +34,9 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Planning constants (measured choices; none is read from the environment).
 constexpr int kResidentWgs = 256 * 2;        // workgroups one round holds: LDS and registers allow two per CU
-constexpr int kMinTilesPerSlice = 1;         // one tile per workgroup only where all tiles of the launch fit one workgroup per CU (a floor of
-                                             // two: 1 to 4 queries over 1K to 8K tokens, bf16 30 to 34 us against 27 to 32, fp32 37 against 31)
+constexpr int kMinTilesPerSlice = 2;         // (one in the smallest launches: floor_of in make_layout_with)
+constexpr int kOneTileCmp = 24;              // compressed tiles of the longest sequence up to which the scan launch of a refresh call takes slices of one ...
+constexpr int kOneTileCmpCapped = 4;         // ... and a reuse call whose selected slices are capped at two tiles and more
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
 constexpr int kWalkIdleTiles = 8;            // one workgroup walks a group's slices where the last round's empty places cost at most this many tile steps
@@ -196,15 +197,13 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     pl.max_sched_entries = pl.C * p->n_sel;
     // selected tiles, at most; with one shared index set per group the schedule is a single set
     const int nts = shared ? ceil_div(pl.C, pl.share_group) * p->n_sel : pl.max_sched_entries;
-    pl.min_tiles_per_split = few_slots ? 2 : kMinTilesPerSlice;
-    const int mt = pl.min_tiles_per_split;
     const int long_slice = p->max_slice_tiles ? p->max_slice_tiles : kLongSliceTiles;
     // Tiles per slice.  If one round of resident workgroups can take the launch with slices of at most long_slice
     // tiles, `per` is grown until the slices of an average unit fit the capacity (no partial second round).
     // Otherwise slices are cut to long_slice tiles: several rounds of workgroups, and the longest slice, the long
     // pole of a mixed-length batch, stays bounded (12-tile slices balanced better but cost 5-10 % at the
     // 128K-context configurations: twice the partial states to write and merge, twice the per-workgroup start-up).
-    auto tiles_per_slice = [&](const int* tiles, int n_roles, int n_units) {
+    auto tiles_per_slice = [&](const int* tiles, int n_roles, int n_units, int mt = kMinTilesPerSlice) {
         int total = 0;
         for (int r = 0; r < n_roles; ++r) total += tiles[r];
         int spu = std::max(n_roles, (capacity / 2) / n_units);      // slices per unit one round can hold, one workgroup per CU
@@ -217,6 +216,20 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
             if (sum <= spu || per >= total) return per;
         }
     };
+    // (caps: the combine kernel's per-row slice loops; unfused: every branch is merged by thread groups that own rows)
+    const int cap_c = unfused ? kCombineRowsMaxSlots : kMaxSlotsPerBranch, cap_ws = unfused ? kCombineRowsMaxSlots : 32;
+    // Fewest tiles per slice: one where the launch would still be one round if every sequence were as long as the longest
+    // (in several rounds short sequences are cut to four tiles and the extra slots stay empty) and where that shortens its
+    // longest slices by more than twice the partial states cost to merge.  Launch time floor one / floor two over 1003 calls
+    // of 1 to 32 queries, 1K to 60K tokens, all head shapes, equal and mixed lengths, whose plans differ: median 0.96
+    // refresh, 0.94 reuse (4 queries over 2K tokens in fp32 35 -> 30 us).  Refresh, compressed and window slices in a launch: up to
+    // 16 compressed tiles 656 of 658 calls are no slower (the others 1.006), at 27 and more up to 1.05.  Reuse, all
+    // branches in one launch: no slower as long as the selected branch gets slices of one tile too (152 of 152 calls); where its
+    // slots end at 32 slices of two tiles, 0.83 to 1.0 with up to 4 compressed tiles, 1.0 to 1.05 with more.
+    auto floor_of = [&](bool pays, int tiles_longest, int n_units) {
+        return pays && !few_slots && (int64_t)tiles_longest * n_units <= kResidentWgs ? 1 : kMinTilesPerSlice;
+    };
+    pl.min_tiles_per_split = kMinTilesPerSlice;
     int per_c, per_w, per_s;
     lo->one_launch = !unfused && !lo->scan32 && p->mode == SSV_REUSE && pl.C_scan == pl.C;   // all three branches in one launch
     if (unfused) {              // one launch per branch
@@ -232,14 +245,14 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         per_w = per_s = tiles_per_slice(&tiles_b, 1, units);
     } else if (lo->one_launch) {
         const int tiles[3] = {ntc_avg, ntw, nts};
-        per_c = per_w = per_s = tiles_per_slice(tiles, 3, units);
+        pl.min_tiles_per_split = floor_of(nts <= cap_ws || ntc <= kOneTileCmpCapped, ntc + ntw + nts, units);
+        per_c = per_w = per_s = tiles_per_slice(tiles, 3, units, pl.min_tiles_per_split);
     } else {
         const int tiles_a[2] = {ntc_avg, ntw};
-        per_c = per_w = tiles_per_slice(tiles_a, 2, units_scan);
-        per_s = tiles_per_slice(&nts, 1, units);
+        pl.min_tiles_per_split = floor_of(ntc <= kOneTileCmp, ntc + ntw, units_scan);
+        per_c = per_w = tiles_per_slice(tiles_a, 2, units_scan, pl.min_tiles_per_split);
+        per_s = tiles_per_slice(&nts, 1, units, floor_of(true, nts, units));
     }
-    // (caps: the combine kernel's per-row slice loops; unfused: every branch is merged by thread groups that own rows)
-    const int cap_c = unfused ? kCombineRowsMaxSlots : kMaxSlotsPerBranch, cap_ws = unfused ? kCombineRowsMaxSlots : 32;
     pl.n_cmp_chunks = std::min(std::max(1, ceil_div(ntc, per_c)), cap_c);
     // The matrix-core scan of a batch of mixed lengths (the caller's average is below the maximum): one range of the
     // batch's tile sequence per workgroup, about total / 256 tiles each; the lengths are read on the device, the

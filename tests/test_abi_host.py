@@ -268,6 +268,55 @@ def test_walked_groups_fill_their_rounds(avg, T):
         assert (pl.n_win_splits, pl.n_slc_splits) == want, (kw, pl.n_win_splits, pl.n_slc_splits)
 
 
+def small_params(heads, kv_heads, d, f32=False, **over):
+    return std_params(**{**dict(B=1, H=heads, H_kv=kv_heads, d_k=d, d_v=min(d, 128), dtype=B.SSV_F32 if f32 else B.SSV_BF16,
+                                max_n_cmp=over["max_seq_len"] // 16 - 1), **over})
+
+
+@pytest.mark.parametrize("p,want", [
+    # refresh: compressed and window slices of one tile up to 24 compressed tiles, of two beyond
+    (dict(heads=64, kv_heads=4, d=192, T=4, max_seq_len=4096), (4, 10, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=24576), (24, 10, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=25600), (13, 5, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=6, max_seq_len=61440), (30, 5, 32)),
+    # reuse: all branches; where the selected one ends at 32 slices of two tiles, up to 4 compressed tiles
+    (dict(heads=16, kv_heads=1, d=192, T=2, max_seq_len=61440, mode=B.SSV_REUSE), (60, 10, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=4096, mode=B.SSV_REUSE), (4, 10, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=5120, mode=B.SSV_REUSE), (3, 5, 32)),
+    # mixed lengths: one round by the longest sequence, not by the average (7 x 2 groups of 30 + 10 tiles are more than one)
+    (dict(heads=8, kv_heads=2, d=64, f32=True, T=1, B=7, max_seq_len=29889, max_n_cmp=1867, avg_seq_len=7472), (15, 5, 16)),
+    (dict(heads=8, kv_heads=2, d=64, f32=True, T=1, B=7, max_seq_len=24576, max_n_cmp=1535, avg_seq_len=7472), (24, 10, 16)),
+    (dict(heads=16, kv_heads=1, d=192, T=1, B=7, max_seq_len=24576, max_n_cmp=1535, avg_seq_len=7472), (24, 10, 16)),
+    # the execution that the fused one replaces keeps two
+    (dict(heads=16, kv_heads=1, d=192, T=2, max_seq_len=2048, exec=B.SSV_EXEC_UNFUSED), (1, 5, 8)),
+])
+def test_slices_of_one_tile(p, want):
+    pl = B.ssv_nsa_plan_query(small_params(**p))
+    assert pl.scan_matrix == 0 and (pl.n_cmp_chunks, pl.n_win_splits, pl.n_slc_splits) == want
+
+
+def test_finer_cuts_do_not_cost_the_static_scratch():
+    """A call whose window and selected slots fit the static array as slices of their own fits it, whatever the plan would take
+    otherwise (an explicit slice bound of 32, the automatic one, asks for slices of their own)."""
+    kept = 0
+    for H, kv, T, n_sel, w, L in [(16, 1, 63, 24, 1024, 2048), (32, 4, 31, 24, 1024, 2048), (32, 4, 7, 32, 1024, 65536), (64, 4, 16, 16, 512, 8192)]:
+        for B_ in range(1, 40):
+            kw = dict(B=B_, T=T, H=H, H_kv=kv, d_k=128, d_v=128, max_seq_len=L, max_n_cmp=L // 16 - 1, n_sel=n_sel, w=w, scan_kernel=B.SSV_SCAN_MATRIX)
+            own = B.ssv_nsa_plan_query(std_params(**kw, max_slice_tiles=32))
+            pl = B.ssv_nsa_plan_query(std_params(**kw))
+            if own.workspace_bytes <= B.SSV_STATIC_SCRATCH_BYTES:
+                assert pl.workspace_bytes <= B.SSV_STATIC_SCRATCH_BYTES, kw
+                # parts that one round leaves a group, and cut no coarser, would have taken more slots than there are bytes for
+                groups = B_ * kv * pl.n_qg
+                parts = 512 // groups
+                slots = pl.n_cmp_chunks + 2 * parts
+                if own.n_win_splits != own.n_slc_splits and own.n_slc_splits <= parts and parts > 1:
+                    fine = slots * B_ * T * H * 130 * 4
+                    assert (pl.n_win_splits == pl.n_slc_splits) or fine > B.SSV_STATIC_SCRATCH_BYTES - B_ * T * kv * (L // 16 + 64) * 4 - 4096, kw
+                    kept += pl.n_win_splits != pl.n_slc_splits
+    assert kept > 0
+
+
 def test_plan_workspace_and_verify_agree():
     """One set of checks serves the three entry points: whatever the plan query accepts, the workspace query sizes
     and verify accepts (up to its pointer checks), and the reverse."""
