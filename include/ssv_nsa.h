@@ -234,7 +234,8 @@ typedef struct ssv_cmp_params {
     int32_t d_k, d_v;        /* row lengths; d_k * elem and d_v * elem must be multiples of 16 bytes */
     int32_t l, d;            /* compression block length and stride (l % d == 0) */
     int32_t dtype;           /* SSV_F32 or SSV_BF16: type of k, v, k_cmp, v_cmp */
-    int32_t max_new_rows;    /* host-side bound (>= 1) on the compressed rows one sequence gains in this call (sizes the grid) */
+    int32_t max_new_rows;    /* host-side bound (>= 1) on the compressed rows one sequence gains in this call; it sizes the grid, so a
+                                tight one keeps a small update cheap (16 tokens in 32 sequences of 128K: 7 us, 42 with the cache's capacity) */
     int32_t kv_capacity;     /* rows of k / v per (sequence, KV head) */
     int32_t cmp_capacity;    /* rows (>= 1) of k_cmp / v_cmp per (sequence, KV head) */
     int64_t k_stride[3], v_stride[3], kc_stride[3], vc_stride[3];

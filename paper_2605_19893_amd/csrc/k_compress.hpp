@@ -21,35 +21,18 @@ struct CompressArgs {
     int rows_per_wg, cap;            // compressed rows per workgroup; row capacity of kc / vc
     int kv_cap, max_new;             // row capacity of k / v; most rows one sequence may gain in this launch
     int k_groups, v_groups;          // 16-byte column groups per K / V row
+    int stream_rows;                 // a sequence that gains more rows than this is built with non-temporal accesses
     float inv_l;
     int64_t k_s[3], v_s[3], kc_s[3], vc_s[3];   // bytes: sequence, KV head, row
 };
 
 __device__ __forceinline__ int complete_cmp_rows(int L, int l, int d) { return L < l ? 0 : (L - l) / d + 1; }
 
-// STREAM: raw rows are loaded and compressed rows stored with the non-temporal hint.  A build reads far more than the
-// last-level cache holds and every row once, so lines that are kept only displace others: 16 sequences of 64K tokens
-// (2.7 GB read, 0.17 written) 536 -> 504 us, 5.3 -> 5.65 TB/s; with 64 chunks per workgroup and ordinary stores 536.  Where
-// the rows read fit the cache they may still be there from the verification that accepted them: 32 sequences gaining
-// up to 512 tokens take 10.2 us with ordinary loads and 10.8 with the hint.
+// Rows [r0, r1) of one (sequence, KV head, K or V).
 template <bool BF16, bool STREAM>
-__global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
+__device__ __forceinline__ void compress_run(const CompressArgs& a, float* s_chunk, const int tid, const int b, const int h, const bool is_v, const int r0,
+                                             const int r1) {
     constexpr int EPG = BF16 ? 8 : 4;           // elements per 16-byte group
-    extern __shared__ __align__(16) char smem[];
-    float* s_chunk = reinterpret_cast<float*>(smem);   // [rows_per_wg + ratio - 1][groups * EPG] chunk sums
-
-    const int tid = threadIdx.x;
-    const int b = blockIdx.y / a.H_kv, h = blockIdx.y % a.H_kv;
-    const bool is_v = blockIdx.z != 0;
-    const int L_before = a.before ? max(a.before[b], 0) : 0;
-    const int L_after = min(max(a.after[b], 0), a.kv_cap);
-    const int c_lo = min(complete_cmp_rows(L_before, a.l, a.d), a.cap);
-    const int c_hi = min(min(complete_cmp_rows(L_after, a.l, a.d), a.cap), c_lo + a.max_new);
-    if (blockIdx.x == 0 && h == 0 && !is_v && tid == 0) a.n_cmp[b] = c_hi;
-    const int r0 = c_lo + blockIdx.x * a.rows_per_wg;
-    const int r1 = min(r0 + a.rows_per_wg, c_hi);
-    if (r0 >= r1) return;
-
     const int groups = is_v ? a.v_groups : a.k_groups;
     const int width = groups * EPG;
     const int64_t src_row = is_v ? a.v_s[2] : a.k_s[2];
@@ -121,6 +104,36 @@ __global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
         if constexpr (STREAM) __builtin_nontemporal_store(packed, to);
         else *to = packed;
     }
+}
+
+// A sequence that gains more than stream_rows rows is built with non-temporal loads and stores: such a launch reads
+// far more than the last-level cache holds and every row once, so lines that are kept only displace others.  16
+// sequences of 64K tokens (2.7 GB read, 0.17 written) 536 -> 503 us, 5.3 -> 5.65 TB/s.  With ordinary stores next to
+// the non-temporal loads 532; what the cache then keeps of the compressed rows for the verification that follows is
+// worth less where they are 168 MB (build and refresh call 648 us without hints, 619, 632 with ordinary stores) and
+// more with 32 mixed lengths of 4K to 128K (905, 879, 859).  Where the rows read fit the cache they may still be
+// there from the verification that accepted them: 32 sequences gaining up to 512 tokens take 10.2 us with ordinary
+// loads and 10.8 with the hint.  What counts is what a sequence gains, not the bound the caller allows for: an update
+// under the bound of a build is an update.
+template <bool BF16>
+__global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
+    extern __shared__ __align__(16) char smem[];
+    float* s_chunk = reinterpret_cast<float*>(smem);   // [rows_per_wg + ratio - 1][row length] chunk sums
+
+    const int tid = threadIdx.x;
+    const int b = blockIdx.y / a.H_kv, h = blockIdx.y % a.H_kv;
+    const bool is_v = blockIdx.z != 0;
+    const int L_before = a.before ? max(a.before[b], 0) : 0;
+    const int L_after = min(max(a.after[b], 0), a.kv_cap);
+    const int c_lo = min(complete_cmp_rows(L_before, a.l, a.d), a.cap);
+    const int c_hi = min(min(complete_cmp_rows(L_after, a.l, a.d), a.cap), c_lo + a.max_new);
+    if (blockIdx.x == 0 && h == 0 && !is_v && tid == 0) a.n_cmp[b] = c_hi;
+    const int r0 = c_lo + blockIdx.x * a.rows_per_wg;
+    const int r1 = min(r0 + a.rows_per_wg, c_hi);
+    if (r0 >= r1) return;
+    // (two bodies: behind a branch at each access the two forms of the store are merged into the ordinary one)
+    if (c_hi - c_lo > a.stream_rows) compress_run<BF16, true>(a, s_chunk, tid, b, h, is_v, r0, r1);      // (uniform per workgroup)
+    else compress_run<BF16, false>(a, s_chunk, tid, b, h, is_v, r0, r1);
 }
 
 }  // namespace ssv

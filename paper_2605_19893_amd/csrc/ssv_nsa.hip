@@ -878,23 +878,21 @@ int ssv_nsa_compress(const void* k, const void* v, void* k_cmp, void* v_cmp, con
     ca.before = committed_before; ca.after = committed_after; ca.n_cmp = n_cmp;
     ca.B = p->B; ca.H_kv = p->H_kv; ca.l = p->l; ca.d = p->d; ca.ratio = ratio;
     // 32 chunks per workgroup: with 16 or 24 column groups per row the chunk tasks fill whole passes of 256 threads
-    const int d_max = std::max(p->d_k, p->d_v);
-    const bool streams = (double)p->max_new_rows * p->d * (p->d_k + p->d_v) * es * p->B * p->H_kv > (double)kLastLevelCache;
     ca.rows_per_wg = std::min(std::max(1, 33 - ratio), p->max_new_rows); ca.cap = p->cmp_capacity; ca.kv_cap = p->kv_capacity;
     ca.max_new = p->max_new_rows;
     ca.k_groups = p->d_k * es / 16; ca.v_groups = p->d_v * es / 16;
     ca.inv_l = 1.0f / (float)p->l;
+    // rows per sequence whose raw rows, over the batch, are as many bytes as the last-level cache holds
+    ca.stream_rows = (int)((double)kLastLevelCache / ((double)p->B * p->H_kv * p->d * (p->d_k + p->d_v) * es));
     for (int j = 0; j < 3; ++j) {
         ca.k_s[j] = p->k_stride[j] * es; ca.v_s[j] = p->v_stride[j] * es;
         ca.kc_s[j] = p->kc_stride[j] * es; ca.vc_s[j] = p->vc_stride[j] * es;
     }
-    const size_t lds = (size_t)(ca.rows_per_wg + ratio - 1) * d_max * sizeof(float);
+    const size_t lds = (size_t)(ca.rows_per_wg + ratio - 1) * std::max(p->d_k, p->d_v) * sizeof(float);
     if (lds > 64 * 1024) return SSV_EUNSUPPORTED;
     const dim3 grid(ceil_div(p->max_new_rows, ca.rows_per_wg), p->B * p->H_kv, 2);
     if (grid.y > 65535) return SSV_EUNSUPPORTED;
-    const auto kernel = p->dtype == SSV_BF16 ? (streams ? k_compress<true, true> : k_compress<true, false>)
-                                             : (streams ? k_compress<false, true> : k_compress<false, false>);
-    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, (hipStream_t)stream, ca);
+    hipLaunchKernelGGL((p->dtype == SSV_BF16 ? k_compress<true> : k_compress<false>), grid, dim3(kThreads), lds, (hipStream_t)stream, ca);
     return hipGetLastError() == hipSuccess ? SSV_OK : SSV_ELAUNCH;
 }
 

@@ -98,8 +98,8 @@ def test_full_build_fp32_and_other_ratios(torch_mod):
 
 @pytest.mark.parametrize("dtype,H_kv,d_k,d_v,l,d", [("bf16", 4, 192, 128, 32, 16), ("f32", 4, 64, 64, 32, 16), ("bf16", 2, 128, 128, 64, 8)])
 def test_builds_that_may_outgrow_the_cache(torch_mod, dtype, H_kv, d_k, d_v, l, d):
-    """The streaming form (chosen by the rows the caller allows for: non-temporal loads and stores): run
-    lengths just below, at and above a workgroup's rows, none at all, and an update that starts inside a run."""
+    """A bound on the new rows as a build larger than the last-level cache has it: run lengths just below, at and above a
+    workgroup's rows, none at all, and an update that starts inside a run."""
     rows = 33 - l // d
     allowed = (300 << 20) // (4 * H_kv * d * (d_k + d_v) * (2 if dtype == "bf16" else 4))
     tokens = lambda n: (n - 1) * d + l
@@ -107,6 +107,52 @@ def test_builds_that_may_outgrow_the_cache(torch_mod, dtype, H_kv, d_k, d_v, l, 
                  [tokens(rows - 1), tokens(rows), tokens(rows + 1), tokens(2 * rows + 1) + 3], 21, max_new_rows=allowed)
     run_compress(torch_mod, dtype, 4, H_kv, d_k, d_v, l, d, tokens(2 * rows + 1), [l - 1, tokens(3), 0, tokens(rows)],
                  [l, tokens(rows + 4), l - 1, tokens(2 * rows + 1)], 22, max_new_rows=allowed)
+
+
+@pytest.mark.parametrize("dtype,H_kv,d_k,d_v,l,d", [("bf16", 4, 192, 128, 32, 16), ("f32", 4, 64, 64, 32, 16), ("bf16", 4, 128, 128, 64, 8)])
+def test_streaming_builds_equal_updates(torch_mod, dtype, H_kv, d_k, d_v, l, d):
+    """Sequences that gain more rows than the last-level cache holds for the batch are built with non-temporal accesses, the
+    others of the launch are not; either way every row is, bit for bit, what small updates give (which the other tests
+    compare with the oracle).  Around the line: one row below, at and above it; runs that end inside a workgroup's rows."""
+    import paper_2605_19893_amd as P
+    torch = torch_mod
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    B = 5
+    line = (256 << 20) // (B * H_kv * d * (d_k + d_v) * (2 if dtype == "bf16" else 4))
+    tokens = lambda n: (n - 1) * d + l
+    lens = [tokens(line), tokens(line + 1), tokens(line + 77) + d - 1, 0, tokens(40)]
+    S = max(lens)
+    cap = oc.n_cmp_rows(S, l, d)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31)
+    k = torch.randn((B, H_kv, S, d_k), generator=g, device="cuda", dtype=tdt)
+    v = torch.randn((B, H_kv, S, d_v), generator=g, device="cuda", dtype=tdt)
+    stream = torch.cuda.current_stream().cuda_stream
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")
+
+    def caches():
+        return [torch.full((B, H_kv, cap, w), 7.0, dtype=tdt, device="cuda") for w in (d_k, d_v)]
+
+    def update(kc, vc, before, after, max_new):
+        p = P.make_cmp_params(B=B, H_kv=H_kv, d_k=d_k, d_v=d_v, l=l, d=d, dtype=P.SSV_BF16 if dtype == "bf16" else P.SSV_F32, max_new_rows=max_new,
+                              kv_capacity=S, cmp_capacity=cap, k_stride=k.stride()[:3], v_stride=v.stride()[:3],
+                              kc_stride=kc.stride()[:3], vc_stride=vc.stride()[:3])
+        n_cmp = torch.full((B,), -9, dtype=torch.int32, device="cuda")
+        P.ssv_nsa_compress(k, v, kc, vc, None if before is None else i32(before), i32(after), n_cmp, p, stream)
+        torch.cuda.synchronize()
+        assert n_cmp.tolist() == [oc.n_cmp_rows(x, l, d) for x in after]
+
+    print(f"[run] compress stream {dtype} lens={lens} line={line}", flush=True)
+    built, stepped = caches(), caches()
+    update(*built, None, lens, cap)
+    step = tokens(line // 3)
+    at = [0] * B
+    while at != lens:
+        nxt = [min(x, a + step) for a, x in zip(at, lens)]
+        update(*stepped, at, nxt, line // 2)
+        at = nxt
+    for x, y in zip(built, stepped):
+        assert torch.equal(x, y)
 
 
 def test_incremental_updates_and_deferred_commit(torch_mod):
