@@ -17,8 +17,9 @@ constexpr int kTile = 64;       // KV rows per streamed tile (= one selection bl
 constexpr int kMaxT = 128;
 
 // Brings the kernel's argument block into the scalar cache in one memory round trip.  The compiler loads arguments where
-// they are first used, and at the start of a launch every 64-byte line of the block is a miss of its own; a wavefront
-// that meets its five or six lines one after the other spends longer on them than on its first tile.
+// they are first used, and at the start of a launch every 64-byte line of the block is a miss of its own (two or three lines
+// in the combine kernels).  Combine launches with it and without: 6.1 against 6.4 us, 8.8 / 9.1, 13.1 / 13.7 and 25.6 / 26.2;
+// no difference in the launches of 4 to 5 us, which wait longer for their statistics, nor in k_stream (six lines).
 template <typename Args>
 __device__ __forceinline__ void touch_args() {
     const auto* p = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -28,19 +29,19 @@ __device__ __forceinline__ void touch_args() {
     asm volatile("" ::"s"(any));
 }
 
-// Division of a non-negative number below 2^31 by a divisor the host knows: n / d = n * mul >> shift with
-// shift = 31 + s, 2^s >= d, mul = ceil(2^shift / d) < 2^32 (exact: the error of mul is below d <= 2^s, so n times it stays
-// below 2^shift).  Three instructions instead of the forty of a 32-bit division or the hundreds of a 64-bit one.
+// Division of a non-negative number below 2^31 by a divisor the host knows (division by an invariant integer through a
+// rounded-up reciprocal, Granlund and Montgomery 1994): n / d = n * mul >> shift with shift = 31 + s, 2^s >= d,
+// mul = ceil(2^shift / d) < 2^32 (exact: the error of mul is below d <= 2^s, so n times it stays below 2^shift).  Three
+// instructions instead of the forty of a 32-bit division or the hundreds of a 64-bit one.
 struct FastDiv {
-    uint32_t d, mul, shift;
+    uint32_t mul, shift;
     __host__ static FastDiv of(int divisor) {
         const uint32_t dv = divisor > 0 ? (uint32_t)divisor : 1u;
         uint32_t s = 0;
         while ((1ull << s) < dv) ++s;
-        return FastDiv{dv, (uint32_t)(((1ull << (31 + s)) + dv - 1) / dv), 31 + s};
+        return FastDiv{(uint32_t)(((1ull << (31 + s)) + dv - 1) / dv), 31 + s};
     }
     __host__ __device__ __forceinline__ int div(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
-    __host__ __device__ __forceinline__ int mod(int n) const { return n - div(n) * (int)d; }
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
