@@ -9,7 +9,7 @@ queries: the latency row), cfg2 (B=16, 64K, 4 queries: the bandwidth-bound batch
 cfg3 (B=4, 128K, a 40-node draft tree) and cfg4 (B=32, mixed 4K-128K, 16 queries), every one with its
 parity check against the fp64 oracle, per-call statistics, per-kernel durations and both roofline
 fractions per kernel (HBM bytes and MFMA flops of the method against the chip's peaks).  One JSON line
-is printed.
+is printed, with the headline; everything measured goes to bench_details.json (--details).
 
 Cold numbers rotate over enough copies of the inputs that the bytes touched between two uses of a copy
 exceed 512 MB, twice the 256 MB last-level cache; warm numbers reuse one copy.
@@ -577,8 +577,44 @@ LABELS = {
 }
 
 
+def report(args, results, order, headline, base, copy_gbs, extra):
+    """(the printed line, everything measured).  The line stays under 4 KB, so that whoever keeps only the end of the output
+    has all of it: the headline with its roofline, parity and baseline, and the times per call of the other workloads."""
+    main_res = results[headline]
+    refresh = main_res["modes"]["refresh"]
+    line = {
+        "metric": "verified query-tokens/s, NSA verify attention (refresh path: routing + selected/window/compressed + gates)",
+        "value": refresh["tokens_per_s_cold"], "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
+        "ms_per_step": refresh["us_per_call_cold"] / 1e3, "higher_is_better": True, "scaling": "weak",
+        "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
+        "config": {"workload": main_res["workload"], "mode": "refresh", "cache": "cold (rotating input copies)"},
+        "roofline": main_res["roofline"],
+        "cpu_baseline": base,
+        "us_per_call": refresh["us_per_call_cold"],
+        "hbm_frac_whole_call": refresh["hbm_frac_whole_call_cold"],
+        "parity": main_res.get("parity"),
+        "us_per_call_cold": {t: {m: round(r["us_per_call_cold"], 2) for m, r in results[t]["modes"].items()} for t in order},
+        "device_copy_GBs": copy_gbs,
+    }
+    details = {
+        **line,
+        "plan": refresh["plan"],
+        "us_per_call_median_p10_p90_with_an_event_per_call": [refresh["us_per_call_cold_median"], refresh["us_per_call_cold_p10"],
+                                                              refresh["us_per_call_cold_p90"]],
+        "algorithmic_bytes": main_res["algorithmic_bytes"],
+        "kernel_roofs_refresh": main_res["kernel_roofs_refresh"],
+        "modes": main_res["modes"],
+        "cold_rotation": main_res["cold_rotation"],
+        "other_workloads": [results[t] for t in order if t != headline],
+        **extra,
+    }
+    return line, details
+
+
 def main():
     ap = argparse.ArgumentParser()
+    ap.add_argument("--details", default=os.path.join(ROOT, "bench_details.json"),
+                    help="file that takes everything measured as one JSON object (empty: none); the printed line holds the headline")
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=200, help="timed calls of the headline workload (the others: 100)")
     ap.add_argument("--warmup", type=int, default=20)
@@ -664,7 +700,6 @@ def main():
         print(f"[bench] {tag}: refresh {res['modes']['refresh']['us_per_call_cold']:.1f} us, reuse "
               f"{res['modes']['reuse']['us_per_call_cold']:.1f} us per call", file=sys.stderr, flush=True)
         del case
-    main_res = results[headline]
     extra = {}
     if not args.only and not args.no_extra:
         extra["approx_shared_index_variant"] = shared_index_study(torch, oracle, si, 8, (0.0, 0.9), 4, 100, args.warmup)
@@ -672,29 +707,13 @@ def main():
         extra["paper_kernel_workload_reduced_grid"] = kernel_workload_study(torch, oracle, si, 100, 10, contexts=(8192, 65536),
                                                                            gammas=(4, 64), overlaps=(3, 6, 10))
 
-    refresh = main_res["modes"]["refresh"]
-    line = {
-        "metric": "verified query-tokens/s, NSA verify attention (refresh path: routing + selected/window/compressed + gates)",
-        "value": refresh["tokens_per_s_cold"], "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
-        "ms_per_step": refresh["us_per_call_cold"] / 1e3, "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
-        "config": {"workload": main_res["workload"], "mode": "refresh", "cache": "cold (rotating input copies)",
-                   "plan": refresh["plan"]},
-        "roofline": main_res["roofline"],
-        "cpu_baseline": base,
-        "us_per_call": refresh["us_per_call_cold"],
-        "us_per_call_median_p10_p90_with_an_event_per_call": [refresh["us_per_call_cold_median"], refresh["us_per_call_cold_p10"],
-                                                              refresh["us_per_call_cold_p90"]],
-        "hbm_frac_whole_call": refresh["hbm_frac_whole_call_cold"],
-        "algorithmic_bytes": main_res["algorithmic_bytes"],
-        "parity": main_res.get("parity"),
-        "kernel_roofs_refresh": main_res["kernel_roofs_refresh"],
-        "modes": main_res["modes"],
-        "cold_rotation": main_res["cold_rotation"],
-        "other_workloads": [results[t] for t in order if t != headline],
-        "device_copy_GBs": copy_gbs,
-    }
-    line.update(extra)
+    line, details = report(args, results, order, headline, base, copy_gbs, extra)
+    if args.details:
+        try:
+            with open(args.details, "w") as f:
+                json.dump(details, f)
+        except OSError as e:
+            print(f"[bench] details not written: {e}", file=sys.stderr)
     print(json.dumps(line))
 
 
