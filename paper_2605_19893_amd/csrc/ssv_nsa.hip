@@ -35,8 +35,8 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // Planning constants (measured choices; none is read from the environment).
 constexpr int kResidentWgs = 256 * 2;        // workgroups one round holds: LDS and registers allow two per CU
 constexpr int kMinTilesPerSlice = 2;         // (one in the smallest launches: floor_of in make_layout_with)
-constexpr int kOneTileCmp = 24;              // compressed tiles of the longest sequence up to which the scan launch of a refresh call takes slices of one ...
-constexpr int kOneTileCmpCapped = 4;         // ... and a reuse call whose selected slices are capped at two tiles and more
+constexpr int kOneTileCmp[2] = {20, 48};     // compressed tiles of the longest sequence up to which the scan launch of a refresh call takes slices of one, bf16 and fp32 ...
+constexpr int kOneTileCmpCapped = 4;         // ... and a reuse call whose selected branch has no slot left for shorter slices
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
 constexpr int kWalkIdleTiles = 8;            // one workgroup walks a group's slices where the last round's empty places cost at most this many tile steps
@@ -220,12 +220,12 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     const int cap_c = unfused ? kCombineRowsMaxSlots : kMaxSlotsPerBranch, cap_ws = unfused ? kCombineRowsMaxSlots : 32;
     // Fewest tiles per slice: one where the launch would still be one round if every sequence were as long as the longest
     // (in several rounds short sequences are cut to four tiles and the extra slots stay empty) and where that shortens its
-    // longest slices by more than twice the partial states cost to merge.  Launch time floor one / floor two over 1003 calls
-    // of 1 to 32 queries, 1K to 60K tokens, all head shapes, equal and mixed lengths, whose plans differ: median 0.96
-    // refresh, 0.94 reuse (4 queries over 2K tokens in fp32 35 -> 30 us).  Refresh, compressed and window slices in a launch: up to
-    // 16 compressed tiles 656 of 658 calls are no slower (the others 1.006), at 27 and more up to 1.05.  Reuse, all
-    // branches in one launch: no slower as long as the selected branch gets slices of one tile too (152 of 152 calls); where its
-    // slots end at 32 slices of two tiles, 0.83 to 1.0 with up to 4 compressed tiles, 1.0 to 1.05 with more.
+    // longest slices by more than twice the partial states cost to merge.  Calls with a floor of one against two, 2000 of 1 to
+    // 64 queries over 1K to 128K tokens of all head shapes, equal and mixed lengths: refresh, compressed and window slices in
+    // a launch: bf16 0.96 of the time up to 8 compressed tiles, 0.97 at 16, 1.00 at 20 to 28 and 1.02 to 1.05 at 48 and more
+    // (one KV head of 16 query heads); fp32, whose tile steps take twice as long, 0.92 up to 8, 0.94 to 24 and still 0.97 at
+    // 48, no difference beyond.  Reuse, all branches in one launch: 0.90 (fp32 0.78) where the selected branch gets more slices by it,
+    // whatever the others; where it has its 32 slots either way, 0.82 to 0.96 with up to 4 compressed tiles, 1.0 to 1.05 with more.
     auto floor_of = [&](bool pays, int tiles_longest, int n_units) {
         return pays && !few_slots && (int64_t)tiles_longest * n_units <= kResidentWgs ? 1 : kMinTilesPerSlice;
     };
@@ -245,11 +245,11 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         per_w = per_s = tiles_per_slice(&tiles_b, 1, units);
     } else if (lo->one_launch) {
         const int tiles[3] = {ntc_avg, ntw, nts};
-        pl.min_tiles_per_split = floor_of(nts <= cap_ws || ntc <= kOneTileCmpCapped, ntc + ntw + nts, units);
+        pl.min_tiles_per_split = floor_of(ceil_div(nts, 2) < cap_ws || ntc <= kOneTileCmpCapped, ntc + ntw + nts, units);
         per_c = per_w = per_s = tiles_per_slice(tiles, 3, units, pl.min_tiles_per_split);
     } else {
         const int tiles_a[2] = {ntc_avg, ntw};
-        pl.min_tiles_per_split = floor_of(ntc <= kOneTileCmp, ntc + ntw, units_scan);
+        pl.min_tiles_per_split = floor_of(ntc <= kOneTileCmp[p->dtype == SSV_F32], ntc + ntw, units_scan);
         per_c = per_w = tiles_per_slice(tiles_a, 2, units_scan, pl.min_tiles_per_split);
         per_s = tiles_per_slice(&nts, 1, units, floor_of(true, nts, units));
     }

@@ -274,19 +274,22 @@ def small_params(heads, kv_heads, d, f32=False, **over):
 
 
 @pytest.mark.parametrize("p,want", [
-    # refresh: compressed and window slices of one tile up to 24 compressed tiles, of two beyond
+    # refresh: compressed and window slices of one tile up to 20 compressed tiles (fp32: 48), of two beyond
     (dict(heads=64, kv_heads=4, d=192, T=4, max_seq_len=4096), (4, 10, 32)),
-    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=24576), (24, 10, 32)),
-    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=25600), (13, 5, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=20480), (20, 10, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=21504), (11, 5, 32)),
+    (dict(heads=4, kv_heads=1, d=64, f32=True, T=4, max_seq_len=49152), (48, 10, 32)),
+    (dict(heads=4, kv_heads=1, d=64, f32=True, T=4, max_seq_len=50176), (25, 5, 32)),
     (dict(heads=16, kv_heads=1, d=192, T=6, max_seq_len=61440), (30, 5, 32)),
-    # reuse: all branches; where the selected one ends at 32 slices of two tiles, up to 4 compressed tiles
+    # reuse: all branches; where the selected one has its 32 slots either way, up to 4 compressed tiles
     (dict(heads=16, kv_heads=1, d=192, T=2, max_seq_len=61440, mode=B.SSV_REUSE), (60, 10, 32)),
+    (dict(heads=8, kv_heads=2, d=64, f32=True, T=3, max_seq_len=12288, mode=B.SSV_REUSE), (12, 10, 32)),
     (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=4096, mode=B.SSV_REUSE), (4, 10, 32)),
     (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=5120, mode=B.SSV_REUSE), (3, 5, 32)),
     # mixed lengths: one round by the longest sequence, not by the average (7 x 2 groups of 30 + 10 tiles are more than one)
     (dict(heads=8, kv_heads=2, d=64, f32=True, T=1, B=7, max_seq_len=29889, max_n_cmp=1867, avg_seq_len=7472), (15, 5, 16)),
     (dict(heads=8, kv_heads=2, d=64, f32=True, T=1, B=7, max_seq_len=24576, max_n_cmp=1535, avg_seq_len=7472), (24, 10, 16)),
-    (dict(heads=16, kv_heads=1, d=192, T=1, B=7, max_seq_len=24576, max_n_cmp=1535, avg_seq_len=7472), (24, 10, 16)),
+    (dict(heads=16, kv_heads=1, d=192, T=1, B=7, max_seq_len=20480, max_n_cmp=1279, avg_seq_len=7472), (20, 10, 16)),
     # the execution that the fused one replaces keeps two
     (dict(heads=16, kv_heads=1, d=192, T=2, max_seq_len=2048, exec=B.SSV_EXEC_UNFUSED), (1, 5, 8)),
 ])
