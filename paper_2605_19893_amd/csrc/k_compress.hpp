@@ -21,7 +21,7 @@ struct CompressArgs {
     int rows_per_wg, cap;            // compressed rows per workgroup; row capacity of kc / vc
     int kv_cap, max_new;             // row capacity of k / v; most rows one sequence may gain in this launch
     int k_groups, v_groups;          // 16-byte column groups per K / V row
-    int stream_rows;                 // a sequence that gains more rows than this is built with non-temporal accesses
+    int stream_rows;                 // mean rows per sequence from which a launch outgrows the last-level cache
     float inv_l;
     int64_t k_s[3], v_s[3], kc_s[3], vc_s[3];   // bytes: sequence, KV head, row
 };
@@ -106,17 +106,18 @@ __device__ __forceinline__ void compress_run(const CompressArgs& a, float* s_chu
     }
 }
 
-// A sequence that gains more than stream_rows rows is built with non-temporal loads and stores: such a launch reads
-// far more than the last-level cache holds and every row once, so lines that are kept only displace others.  16
-// sequences of 64K tokens (2.7 GB read, 0.17 written) 536 -> 503 us, 5.3 -> 5.65 TB/s.  With ordinary stores next to
-// the non-temporal loads 532; what the cache then keeps of the compressed rows for the verification that follows is
-// worth less where they are 168 MB (build and refresh call 648 us without hints, 619, 632 with ordinary stores) and
-// more with 32 mixed lengths of 4K to 128K (905, 879, 859).  Where the rows read fit the cache they may still be
-// there from the verification that accepted them: 32 sequences gaining up to 512 tokens take 10.2 us with ordinary
-// loads and 10.8 with the hint.  What counts is what a sequence gains, not the bound the caller allows for: an update
-// under the bound of a build is an update.
+// The long sequences of a launch that reads more raw rows than the last-level cache holds are built with non-temporal
+// loads and stores: every row is read once, so lines that are kept only displace others.  16 sequences of 64K tokens
+// (2.7 GB read, 0.17 written) 536 -> 503 us, 5.3 -> 5.65 TB/s.  With ordinary stores next to the non-temporal loads
+// 532; what the cache then keeps of the compressed rows for the verification that follows is worth less where they
+// are 168 MB (build and refresh call 648 us without hints, 619, 632 with ordinary stores) and more with 32 mixed
+// lengths of 4K to 128K (905, 879, 859).  Where the rows read fit the cache they may still be there from the
+// verification that accepted them: 32 sequences gaining up to 512 tokens take 10.2 us with ordinary loads and 10.8
+// with the hint.  What counts is what the sequences gain, not the bound the caller allows for (an update under the
+// bound of a build is an update) nor the longest of them (17 sequences of 256 to 7232 tokens, 126 MB: 19.2 us with
+// ordinary accesses, 20.6 with the hint).
 template <bool BF16>
-__global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
+__global__ void __launch_bounds__(kThreads, 8) k_compress(const CompressArgs a) {
     extern __shared__ __align__(16) char smem[];
     float* s_chunk = reinterpret_cast<float*>(smem);   // [rows_per_wg + ratio - 1][row length] chunk sums
 
@@ -131,9 +132,24 @@ __global__ void __launch_bounds__(kThreads) k_compress(const CompressArgs a) {
     const int r0 = c_lo + blockIdx.x * a.rows_per_wg;
     const int r1 = min(r0 + a.rows_per_wg, c_hi);
     if (r0 >= r1) return;
-    // (two bodies: behind a branch at each access the two forms of the store are merged into the ordinary one)
-    if (c_hi - c_lo > a.stream_rows) compress_run<BF16, true>(a, s_chunk, tid, b, h, is_v, r0, r1);      // (uniform per workgroup)
-    else compress_run<BF16, false>(a, s_chunk, tid, b, h, is_v, r0, r1);
+    bool stream = c_hi - c_lo > a.stream_rows;      // (uniform per workgroup)
+    if (__builtin_expect(stream, 0)) {       // a long sequence: what the launch gains, from all sequences or 64 spread over them
+        const int lane = tid & 63, n = min(a.B, 64);
+        int rows = 0;
+        if (lane < n) {
+            const int x = (int)((int64_t)lane * a.B / n);
+            const int lo = min(complete_cmp_rows(a.before ? max(a.before[x], 0) : 0, a.l, a.d), a.cap);
+            rows = max(0, min(min(complete_cmp_rows(min(max(a.after[x], 0), a.kv_cap), a.l, a.d), a.cap) - lo, a.max_new));
+        }
+        float sum = (float)rows;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+        stream = __builtin_amdgcn_readfirstlane(sum > (float)a.stream_rows * (float)n);      // (every lane has the same sum)
+    }
+    // (two bodies: behind a branch at each access the two forms of the store are merged into the ordinary one; eight wavefronts
+    // per SIMD asked for, the registers of one body alone: fp32 builds of 36 MB 8.8 -> 8.6 us)
+    if (__builtin_expect(!stream, 1)) compress_run<BF16, false>(a, s_chunk, tid, b, h, is_v, r0, r1);
+    else compress_run<BF16, true>(a, s_chunk, tid, b, h, is_v, r0, r1);
 }
 
 }  // namespace ssv

@@ -111,16 +111,16 @@ def test_builds_that_may_outgrow_the_cache(torch_mod, dtype, H_kv, d_k, d_v, l, 
 
 @pytest.mark.parametrize("dtype,H_kv,d_k,d_v,l,d", [("bf16", 4, 192, 128, 32, 16), ("f32", 4, 64, 64, 32, 16), ("bf16", 4, 128, 128, 64, 8)])
 def test_streaming_builds_equal_updates(torch_mod, dtype, H_kv, d_k, d_v, l, d):
-    """Sequences that gain more rows than the last-level cache holds for the batch are built with non-temporal accesses, the
-    others of the launch are not; either way every row is, bit for bit, what small updates give (which the other tests
-    compare with the oracle).  Around the line: one row below, at and above it; runs that end inside a workgroup's rows."""
+    """Long sequences of a launch that outgrows the last-level cache are built with non-temporal accesses, the others are not;
+    either way every row is, bit for bit, what small updates give (which the other tests compare with the oracle).  Around
+    the line: as many rows as the mean that fills the cache, one and more above it; runs that end inside a workgroup's rows."""
     import paper_2605_19893_amd as P
     torch = torch_mod
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     B = 5
     line = (256 << 20) // (B * H_kv * d * (d_k + d_v) * (2 if dtype == "bf16" else 4))
     tokens = lambda n: (n - 1) * d + l
-    lens = [tokens(line), tokens(line + 1), tokens(line + 77) + d - 1, 0, tokens(40)]
+    lens = [tokens(line), tokens(line + 1), tokens(4 * line + 77) + d - 1, 0, tokens(40)]
     S = max(lens)
     cap = oc.n_cmp_rows(S, l, d)
     g = torch.Generator(device="cuda")
@@ -145,11 +145,11 @@ def test_streaming_builds_equal_updates(torch_mod, dtype, H_kv, d_k, d_v, l, d):
     print(f"[run] compress stream {dtype} lens={lens} line={line}", flush=True)
     built, stepped = caches(), caches()
     update(*built, None, lens, cap)
-    step = tokens(line // 3)
+    step = tokens(line // 2)
     at = [0] * B
     while at != lens:
         nxt = [min(x, a + step) for a, x in zip(at, lens)]
-        update(*stepped, at, nxt, line // 2)
+        update(*stepped, at, nxt, line)
         at = nxt
     for x, y in zip(built, stepped):
         assert torch.equal(x, y)
