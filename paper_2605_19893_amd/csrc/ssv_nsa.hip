@@ -39,7 +39,8 @@ constexpr int kOneTileCmp[2] = {20, 48};     // compressed tiles of the longest 
 constexpr int kOneTileCmpCapped = 4;         // ... and a reuse call whose selected branch has no slot left for shorter slices
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
-constexpr int kWalkIdleTiles = 8;            // one workgroup walks a group's slices where the last round's empty places cost at most this many tile steps
+constexpr int kWalkIdleTiles = 6;            // one workgroup walks a group's slices where the last round's empty places cost at most this many tile steps
+constexpr int kWalkMaxTiles = 100;           // ... and a group has at most this many tiles
 constexpr int kImportanceWgs = 512;          // one round of the importance pass (more, shorter workgroups measured slower)
 constexpr int kTopnInSlcMaxWgs = 256;        // SSV_TOPN_AUTO: select inside the selected-branch launch up to this many workgroups
                                              // (twice as many when a wavefront has one query to select for)
@@ -224,8 +225,9 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     // 64 queries over 1K to 128K tokens of all head shapes, equal and mixed lengths: refresh, compressed and window slices in
     // a launch: bf16 0.96 of the time up to 8 compressed tiles, 0.97 at 16, 1.00 at 20 to 28 and 1.02 to 1.05 at 48 and more
     // (one KV head of 16 query heads); fp32, whose tile steps take twice as long, 0.92 up to 8, 0.94 to 24 and still 0.97 at
-    // 48, no difference beyond.  Reuse, all branches in one launch: 0.90 (fp32 0.78) where the selected branch gets more slices by it,
-    // whatever the others; where it has its 32 slots either way, 0.82 to 0.96 with up to 4 compressed tiles, 1.0 to 1.05 with more.
+    // 48, no difference beyond.  Reuse, all branches in one launch: 0.90 (fp32 0.78) where the selected branch gets more
+    // slices by it, up to the 64 slots of the compressed one; where it has its 32 slots either way, 0.82 to 0.96 with up to 4
+    // compressed tiles, 1.0 to 1.05 with more.
     auto floor_of = [&](bool pays, int tiles_longest, int n_units) {
         return pays && !few_slots && (int64_t)tiles_longest * n_units <= kResidentWgs ? 1 : kMinTilesPerSlice;
     };
@@ -245,7 +247,7 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         per_w = per_s = tiles_per_slice(&tiles_b, 1, units);
     } else if (lo->one_launch) {
         const int tiles[3] = {ntc_avg, ntw, nts};
-        pl.min_tiles_per_split = floor_of(ceil_div(nts, 2) < cap_ws || ntc <= kOneTileCmpCapped, ntc + ntw + nts, units);
+        pl.min_tiles_per_split = floor_of((ceil_div(nts, 2) < cap_ws && ntc <= cap_c) || ntc <= kOneTileCmpCapped, ntc + ntw + nts, units);
         per_c = per_w = per_s = tiles_per_slice(tiles, 3, units, pl.min_tiles_per_split);
     } else {
         const int tiles_a[2] = {ntc_avg, ntw};
@@ -281,19 +283,23 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         // takes, but only where they cut the schedule no coarser than slices of its own would: every slice has one
         // probability that is exactly 1 in bf16, and with fewer slices the result is further off (one part in place of
         // two slices, 32 sequences of 16 queries: 2.148e-3 -> 2.156e-3 of the 64-bit result, the same on every input).
-        // Whole calls against a workgroup per slice (16 queries, groups x parts of 512 places, refresh and reuse): 192 x 2
-        // 141 -> 130 and 115 -> 106 us, 256 x 2 159 -> 138 and 128 -> 110; 176 x 2 157 -> 156 and 121 -> 116; 128 x 4 (32
-        // queries, 8 heads per group) 136 -> 125 and 98 -> 87; 40-node trees 240 x 2 196 -> 173 and 147 -> 126.
+        // Whole calls against a workgroup per slice (16 queries, groups x parts of 512 places, refresh and reuse): 256 x 2
+        // 159 -> 138 and 128 -> 110; 128 x 4 (32 queries, 8 heads per group) 136 -> 125 and 98 -> 87; 40-node trees 240 x 2
+        // 196 -> 173 and 147 -> 126.  Only where these parts fill four fifths of the round: where sequences bring fewer
+        // queries than the batch's capacity, groups are empty and more slices fit a round than the host counts (180 x 2: 33
+        // to 36 queries each 5 % faster, 17 to 36 of them 1 to 7 % slower; 240 x 2 faster either way).
         // Otherwise each branch keeps slices of its own, and in batches of mixed lengths (the caller's average below the
         // maximum) one workgroup walks all slices of a group where one per group nearly fills its rounds: one start-up and
-        // one schedule per group instead of one per slice, the same slices and results.  What it costs is the empty places of the last round: the launch is idle places x tiles of a group / 512
-        // tile steps longer than an even spread, and workgroups this long leave nothing to even that out.  The line of
-        // kWalkIdleTiles lies between (calls in us, a workgroup per slice -> walked)
-        // 464 groups of 75 tiles (7.0: 217 -> 209), 480 (4.7: 231 -> 217), 992 (4.7: 396 -> 390), 1504 (4.7: 486 -> 478), 496 of 139
-        // tiles (4.3: 286 -> 280) and full rounds (512: 257 -> 245, 1024: 403 -> 392, 512 of 139 tiles 281 -> 276, 1024 of
-        // 267 tiles 559 -> 512) on one side and 448 (9.4: 236 -> 234 refresh, 193 -> 196 reuse), 960 (9.4: 387 -> 387), 928
-        // (14: 372 -> 376), 480 of 139 tiles (8.7: 291 -> 288 and 253 -> 254; 8 heads per group 224 -> 227), 896 (19: 354 ->
-        // 362), 640 (56: 273 -> 314) on the other.
+        // one schedule per group instead of one per slice, the same slices and results.  What it costs is the empty places
+        // of the last round: the launch is idle places x tiles of a group / 512 tile steps longer than an even spread, and
+        // workgroups this long leave nothing to even that out.  The line of
+        // kWalkIdleTiles lies between (calls in us, a workgroup per slice -> walked; groups of 75 tiles) 480 groups (4.7: 231 ->
+        // 217), 992 (4.7: 396 -> 390), 1504 (4.7: 486 -> 478) and full rounds (512: 257 -> 245, 1024: 403 -> 392) on one side
+        // and 448 (9.4: 236 -> 234 refresh, 193 -> 196 reuse), 960 (9.4: 387 -> 387), 928 (14: 372 -> 376), 896 (19: 354 ->
+        // 362), 640 (56: 273 -> 314) on the other; 464 (7.0) gains 4 % where every sequence brings all its queries, and 460
+        // (7.5) loses 1 % where they bring half of them and more: groups without queries are empty places too.  With
+        // longer groups they cost more than the walk saves: of 139 tiles, 500 groups, 357 -> 376 us with ragged queries (512
+        // groups of 8 heads with all of them 281 -> 276).
         // Lengths do not enter into it: equal ones gain as much (480 groups of 75 tiles 266 -> 255, 512 351 -> 339) and lose as
         // much (640: 331 -> 371); they keep a workgroup per slice, the plan they have had.
         // Both need launches of two resident workgroups per CU.  At d_k = 64 the kernel takes 157 registers, three fit, and
@@ -305,7 +311,8 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         const int sep_w = std::min(std::max(1, ceil_div(ntw, per_b)), cap_ws), sep_s = std::min(std::max(1, ceil_div(nts, per_b)), cap_ws);
         // (fewer parts than the slice length asks for are longer ones: not past a bound that the caller gave)
         const bool two_per_cu = p->d_k > 64;
-        const bool fewer = two_per_cu && parts > 1 && parts >= sep_s && (!p->max_slice_tiles || ceil_div(ntw + nts, parts) <= p->max_slice_tiles);
+        const bool fewer = two_per_cu && parts > 1 && parts >= sep_s && 5 * units * parts >= 4 * kResidentWgs &&
+                           (!p->max_slice_tiles || ceil_div(ntw + nts, parts) <= p->max_slice_tiles);
         if (units * parts <= kResidentWgs && (parts == parts_all || (fewer && !(few_slots && 2 * parts > sep_w + sep_s)))) {
             lo->joint_parts = parts;
             pl.n_win_splits = pl.n_slc_splits = parts;
@@ -314,7 +321,8 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
             pl.n_win_splits = sep_w;
             pl.n_slc_splits = sep_s;
             const int64_t idle = (int64_t)ceil_div(units, kResidentWgs) * kResidentWgs - units;
-            lo->walk = lo->scan_balanced && two_per_cu && !p->max_slice_tiles && idle * (ntw + nts) <= (int64_t)kWalkIdleTiles * kResidentWgs;
+            lo->walk = lo->scan_balanced && two_per_cu && !p->max_slice_tiles && ntw + nts <= kWalkMaxTiles &&
+                       idle * (ntw + nts) <= (int64_t)kWalkIdleTiles * kResidentWgs;
         }
     }
     // The streaming kernel's compressed scan of a batch of mixed lengths: slices per sequence in proportion to its length,
