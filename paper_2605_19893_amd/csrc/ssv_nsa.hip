@@ -36,7 +36,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr int kResidentWgs = 256 * 2;        // workgroups one round holds: LDS and registers allow two per CU
 constexpr int kMinTilesPerSlice = 2;         // (one in the smallest launches: floor_of in make_layout_with)
 constexpr int kOneTileCmp[2] = {20, 48};     // compressed tiles of the longest sequence up to which the scan launch of a refresh call takes slices of one, bf16 and fp32 ...
-constexpr int kOneTileCmpCapped = 4;         // ... and a reuse call whose selected branch has no slot left for shorter slices
+constexpr int kOneTileCmpCapped = 4;         // ... and a reuse call whose selected branch has all its slots with two tiles already
 constexpr int kMinTilesMultiRound = 4;       // launches of several rounds: slices of a short sequence hold at least this many tiles
 constexpr int kLongSliceTiles = 32;          // slice length once a launch needs several rounds (max_slice_tiles = 0)
 constexpr int kWalkIdleTiles = 6;            // one workgroup walks a group's slices where the last round's empty places cost at most this many tile steps
@@ -225,8 +225,9 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
     // 64 queries over 1K to 128K tokens of all head shapes, equal and mixed lengths: refresh, compressed and window slices in
     // a launch: bf16 0.96 of the time up to 8 compressed tiles, 0.97 at 16, 1.00 at 20 to 28 and 1.02 to 1.05 at 48 and more
     // (one KV head of 16 query heads); fp32, whose tile steps take twice as long, 0.92 up to 8, 0.94 to 24 and still 0.97 at
-    // 48, no difference beyond.  Reuse, all branches in one launch: 0.90 (fp32 0.78) where the selected branch gets more
-    // slices by it, up to the 64 slots of the compressed one; where it has its 32 slots either way, 0.82 to 0.96 with up to 4
+    // 48, no difference beyond.  Reuse, all branches in one launch: 0.90 (fp32 0.78) where the selected branch gets slices of
+    // one tile too, up to the 64 slots of the compressed one; where it only gets more of its 32 slots (three queries) 0.92 to
+    // 0.96 up to the same lines as in refresh calls, 1.03 beyond; where it has them all either way, 0.82 to 0.96 with up to 4
     // compressed tiles, 1.0 to 1.05 with more.
     auto floor_of = [&](bool pays, int tiles_longest, int n_units) {
         return pays && !few_slots && (int64_t)tiles_longest * n_units <= kResidentWgs ? 1 : kMinTilesPerSlice;
@@ -247,7 +248,8 @@ int make_layout_with(const ssv_nsa_params* p, bool few_slots, Layout* lo) {
         per_w = per_s = tiles_per_slice(&tiles_b, 1, units);
     } else if (lo->one_launch) {
         const int tiles[3] = {ntc_avg, ntw, nts};
-        pl.min_tiles_per_split = floor_of((ceil_div(nts, 2) < cap_ws && ntc <= cap_c) || ntc <= kOneTileCmpCapped, ntc + ntw + nts, units);
+        const int most = nts <= cap_ws ? cap_c : ceil_div(nts, 2) < cap_ws ? kOneTileCmp[p->dtype == SSV_F32] : kOneTileCmpCapped;
+        pl.min_tiles_per_split = floor_of(ntc <= most, ntc + ntw + nts, units);
         per_c = per_w = per_s = tiles_per_slice(tiles, 3, units, pl.min_tiles_per_split);
     } else {
         const int tiles_a[2] = {ntc_avg, ntw};

@@ -285,6 +285,7 @@ def small_params(heads, kv_heads, d, f32=False, **over):
     # reuse: all branches; where the selected one has its 32 slots either way, up to 4 compressed tiles
     (dict(heads=16, kv_heads=1, d=192, T=2, max_seq_len=61440, mode=B.SSV_REUSE), (60, 10, 32)),
     (dict(heads=8, kv_heads=2, d=64, f32=True, T=3, max_seq_len=12288, mode=B.SSV_REUSE), (12, 10, 32)),
+    (dict(heads=16, kv_heads=1, d=192, T=3, max_seq_len=21504, mode=B.SSV_REUSE), (11, 5, 24)),
     (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=4096, mode=B.SSV_REUSE), (4, 10, 32)),
     (dict(heads=16, kv_heads=1, d=192, T=4, max_seq_len=5120, mode=B.SSV_REUSE), (3, 5, 32)),
     # mixed lengths: one round by the longest sequence, not by the average (7 x 2 groups of 30 + 10 tiles are more than one)
