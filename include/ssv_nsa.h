@@ -84,7 +84,7 @@ extern "C" {
 #define SSV_K_IMPORTANCE 1    /* refresh only: normalised compressed probabilities summed over the group's heads */
 #define SSV_K_TOPN      2     /* refresh only: block importance + top-n selection; not launched (time 0) when the
                                  selection runs inside SSV_K_STREAM_B, which it does when that launch has at most
-                                 one workgroup per CU */
+                                 one workgroup per CU (two with groups of up to four queries) */
 #define SSV_K_STREAM_B  3     /* selected-block attention over the merged schedule: refresh, and reuse when the scans
                                  of SSV_K_STREAM_A use larger query groups than the selected branch (plan.C_scan > C);
                                  with plan.scan_matrix: selected blocks + window */
