@@ -19,7 +19,9 @@ constexpr int kMaxT = 128;
 // Brings the kernel's argument block into the scalar cache in one memory round trip.  The compiler loads arguments where
 // they are first used, and at the start of a launch every 64-byte line of the block is a miss of its own (two or three lines
 // in the combine kernels).  Combine launches with it and without: 6.1 against 6.4 us, 8.8 / 9.1, 13.1 / 13.7 and 25.6 / 26.2;
-// no difference in the launches of 4 to 5 us, which wait longer for their statistics, nor in k_stream (six lines).
+// no difference in the launches of 4 to 5 us, which wait longer for their statistics.  Before k_stream (six lines, the lengths
+// ahead of the query rows) calls of 35 to 60 us take 0.3 to 0.6 us less with it, but one that is a single launch (all three
+// branches) 0.2 more; the importance pass loses 0.7 us to it, the matrix-core scan does not mind.
 template <typename Args>
 __device__ __forceinline__ void touch_args() {
     const auto* p = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -127,6 +129,28 @@ __device__ __forceinline__ u32x4 lds_read16_at(uint32_t addr) {
     return *reinterpret_cast<__attribute__((address_space(3))) const u32x4*>((uintptr_t)addr);
 }
 
+// 16 bytes per lane from a buffer straight into LDS: lane i's bytes go to lds + 16 i (lds and soff uniform).  The instruction
+// has no register result, only the counter of vector memory operations says when its bytes are there: whoever issues it
+// waits with wait_vmcnt before the barrier that publishes the tile.  Written as assembly because the compiler, where it
+// knows of such a load in flight, waits for all of them before a transposing LDS read and before barriers that have no
+// counted wait in front, so that nothing is fetched ahead.  Its own counted waits become stricter by the loads it does not
+// know: callers let it wait for registers loaded earlier (arrived, below) before they issue what may stay in flight.
+// Five wait states between a scalar register written by a vector instruction and its use here, one behind m0.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"       // (m0 in the clobber list)
+__device__ __forceinline__ void buffer_load_lds16(u32x4 rsrc, uint32_t lds, uint32_t voff, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+#pragma clang diagnostic pop
+template <int N>
+__device__ __forceinline__ void arrived(u32x4 (&r)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(r[i]));
+}
+
 // Tile loaders come in two halves so that the global loads of the next tile can be in flight while the
 // current tile is being computed: *_issue reads into registers, *_commit writes the registers to LDS.
 // All global loads are unconditional (the row index is clamped, the value is zeroed at commit), so they
@@ -232,9 +256,10 @@ struct DirectRowTile {
     // RECOMPUTE: the (row, column) pairs behind the clamped offsets of a partial tile are derived again at every
     // partial tile instead of being kept in registers across the caller's loops (for kernels short of registers).
     template <bool RECOMPUTE = false>
-    __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rsrc, uint32_t tile_off, char* lds_tile, uint32_t g_row_bytes,
+    __device__ __forceinline__ void issue(u32x4 rsrc, uint32_t tile_off, char* lds_tile, uint32_t g_row_bytes,
                                           int valid_rows, int tid) {
-        char* dst = lds_tile + (tid >> 6) * ITERS * 1024;     // wave-uniform
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(lds_tile) + (uint32_t)(tid >> 6) * ITERS * 1024u);
+        const uint32_t soff = __builtin_amdgcn_readfirstlane(tile_off);
         if constexpr (RECOMPUTE) {
             if (valid_rows < kTile) asm volatile("" : "+v"(tid));    // opaque from here on: nothing below can be hoisted
         }
@@ -246,14 +271,30 @@ struct DirectRowTile {
                 where(tid, it, r, c);
                 o = (uint32_t)min(r, valid_rows - 1) * g_row_bytes + (uint32_t)c * 16u;
             }
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(dst + it * 1024), 16,
-                                                     (int)o, (int)tile_off, 0, 0);
+            buffer_load_lds16(rsrc, dst + it * 1024, o, soff);
         }
     }
-    // Raw buffer resource (stride 0, bounds in bytes) over `bytes` bytes at `base`: loads past the end return zero
-    // instead of faulting.
-    __device__ __forceinline__ static __amdgpu_buffer_rsrc_t make_rsrc(const char* base, int64_t bytes) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)min(bytes, (int64_t)0x7fffffff), 0x00020000);
+    // For callers that spread a tile's loads over other work: the offsets of a tile of valid_rows < kTile rows (until the next
+    // init), and instruction `it` of a tile with the offsets as they are.
+    __device__ __forceinline__ void clamp(uint32_t g_row_bytes, int valid_rows, int tid) {
+        asm volatile("" : "+v"(tid));        // (derived here, not kept in registers across the caller's loops)
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) {
+            int r, c;
+            where(tid, it, r, c);
+            off[it] = (uint32_t)min(r, valid_rows - 1) * g_row_bytes + (uint32_t)c * 16u;
+        }
+    }
+    __device__ __forceinline__ void issue_one(int it, u32x4 rsrc, uint32_t tile_off, char* lds_tile, int tid) {
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(lds_tile) + (uint32_t)((tid >> 6) * ITERS + it) * 1024u);
+        buffer_load_lds16(rsrc, dst, off[it], __builtin_amdgcn_readfirstlane(tile_off));
+    }
+    // Raw buffer resource (stride 0, bounds in bytes) over `bytes` bytes at `base`, both uniform: loads past the end return
+    // zero instead of faulting.
+    __device__ __forceinline__ static u32x4 make_rsrc(const char* base, int64_t bytes) {
+        const uint64_t at = (uint64_t)base;
+        return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at), (uint32_t)__builtin_amdgcn_readfirstlane((int)((at >> 32) & 0xffffu)),
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)min(bytes, (int64_t)0x7fffffff)), 0x00020000u};
     }
     // byte offset, inside the tile, of granule column c0 + (kc ^ ...) handled through two per-lane bases: a lane that
     // reads row `row` and granule G of 64-byte chunk kc finds it at base(kc & 1) + kc * 64, with
@@ -388,15 +429,29 @@ struct SeqMeta {
     int L, Tq, n_cmp;
 };
 
+// What the metadata is built from, in registers: fetched ahead of the caller's query rows, so that the wait for it does not
+// include theirs (loads complete in issue order, and a workgroup's query rows are up to 98 KB).  The parents are not among
+// it: a vector register with a load pending in some calls is waited for, with all loads in flight, wherever it is used next.
+struct MetaFetch {
+    int L, Tq, n_cmp;
+};
+__device__ __forceinline__ MetaFetch fetch_tree_meta(int b, int T, const int32_t* seq_lens, const int32_t* n_query, const int32_t* n_cmp) {
+    MetaFetch f;
+    f.L = seq_lens[b];
+    f.n_cmp = n_cmp[b];
+    f.Tq = n_query ? n_query[b] : T;
+    __builtin_amdgcn_sched_barrier(0);       // (what the caller loads next stays behind)
+    return f;
+}
+
 // Lengths read from device memory are clamped to the host-side bounds every buffer and grid was sized with, so that
 // an inconsistent length array cannot take a load past the end of a cache.
-__device__ __forceinline__ SeqMeta build_tree_meta(int tid, int b, int T, const int32_t* seq_lens, const int32_t* n_query,
-                                                   const int32_t* n_cmp, const int32_t* parents, int l, int d, int max_seq_len,
+__device__ __forceinline__ SeqMeta build_tree_meta(int tid, const MetaFetch& f, int b, int T, const int32_t* parents, int l, int d, int max_seq_len,
                                                    int max_n_cmp, int* s_par, int* s_depth, int* s_cmax, AncSet* s_anc) {
     SeqMeta sm;
-    sm.L = min(max(seq_lens[b], 0), max_seq_len);
-    sm.Tq = n_query ? min(max(n_query[b], 0), T) : T;
-    sm.n_cmp = min(max(n_cmp[b], 0), max_n_cmp);
+    sm.L = min(max(f.L, 0), max_seq_len);
+    sm.Tq = min(max(f.Tq, 0), T);
+    sm.n_cmp = min(max(f.n_cmp, 0), max_n_cmp);
     if (parents) {
         if (tid < kMaxT) {
             int par = -1;

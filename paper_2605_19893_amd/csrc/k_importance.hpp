@@ -148,8 +148,8 @@ __global__ void __launch_bounds__(kThreads, 2) k_importance(const ImportanceArgs
         const auto query_of = [&](int j) { return qg * a.C + j; };
         load_q_and_stats(query_of, min(a.C, a.T - qg * a.C));
     }
-    const SeqMeta sm = build_tree_meta(tid, b, a.T, a.seq_lens, a.n_query, a.n_cmp, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth,
-                                       s_cmax, s_anc);
+    const MetaFetch mf = fetch_tree_meta(b, a.T, a.seq_lens, a.n_query, a.n_cmp);
+    const SeqMeta sm = build_tree_meta(tid, mf, b, a.T, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth, s_cmax, s_anc);
     const int Tq = sm.Tq;
     const int n_routed = a.share ? (Tq + a.share - 1) / a.share : Tq;
     const int nq_grp = min(a.C, n_routed - qg * a.C);
@@ -176,8 +176,8 @@ __global__ void __launch_bounds__(kThreads, 2) k_importance(const ImportanceArgs
     // The strips go from global memory straight into a ring of DEPTH tile slots in LDS (buffer loads with the LDS
     // destination: lane-linear, so a lane of any wavefront that reads a strip finds at its own position the 16 bytes
     // of its key and granule), ahead of the tile in use: the registers are taken by the A operands.
-    const __amdgpu_buffer_rsrc_t krsrc =
-        DirectRowTile<Cfg::KROW>::make_rsrc(a.kc + b * a.kc_s[0] + g * a.kc_s[1], (int64_t)sm.n_cmp * a.kc_s[2]);
+    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(a.kc + b * a.kc_s[0] + g * a.kc_s[1]), 0,
+                                                                           (int)min((int64_t)sm.n_cmp * a.kc_s[2], (int64_t)0x7fffffff), 0x00020000);
     const uint32_t krow = (uint32_t)a.kc_s[2];
     constexpr int STRIP = KCH * 1024, SLOT = 4 * STRIP;
     auto issue_strip = [&](int tile) {
@@ -448,10 +448,12 @@ struct Importance32Cfg {
 };
 
 // NW: wavefronts per workgroup.  Eight (RW = 4 only) give every wavefront one row tile and both key tiles, four
-// wavefronts per SIMD with two workgroups per CU: measured on the device, one wavefront issues a 32x32x16 matrix
-// instruction every 64 clocks at best and its vector instructions at about half the rate a SIMD reaches with several
-// wavefronts, so a tile step takes a wavefront the sum of its own matrix and vector work whatever else the SIMD holds;
-// halving the work per wavefront halves the step, as long as the registers (128 per lane) allow four per SIMD.
+// wavefronts per SIMD with two workgroups per CU, as long as the registers (128 per lane) allow that many: their matrix and
+// vector phases overlap by themselves, block by block.  With two per SIMD (NW = 4, two key tiles) the exponentials of a block
+// are put between the matrix instructions of the next.
+// Measured (4 sequences of 40 queries over 128K tokens): 47.5 us with each fragment read right before its matrix instruction
+// and the statistics fetched block by block behind the first tiles, 44.8 with the reads ahead, 43.4 with the statistics
+// fetched at the start; 32 mixed sequences of 16 queries 46.5 -> 43.3.
 template <int DK, int HGM, int RW, int NW = 4>
 __global__ void __launch_bounds__(64 * NW, NW == 8 ? 1 : 2) __attribute__((amdgpu_waves_per_eu(NW == 8 ? 4 : 2, NW == 8 ? 4 : 8)))
 k_importance32(const ImportanceArgs a) {
@@ -498,6 +500,7 @@ k_importance32(const ImportanceArgs a) {
     // A operands: row n of every row tile of this wavefront, all contraction steps.  When every query is routed the
     // rows are known before the sequence's metadata, and their loads overlap its latency (queries past the
     // sequence's count are loaded too, they exist in the buffer; nothing of theirs is used).
+    const MetaFetch mf = fetch_tree_meta(b, a.T, a.seq_lens, a.n_query, a.n_cmp);
     u32x4 qf[RTW][STEPS];
     auto load_q = [&](auto query_of, int nq) {
 #pragma unroll
@@ -510,12 +513,34 @@ k_importance32(const ImportanceArgs a) {
             for (int st = 0; st < STEPS; ++st) qf[t][st] = *reinterpret_cast<const u32x4*>(a.q + qoff + st * 32 + hb * 16);
         }
     };
+    // Softmax statistics of the compressed scan: one row per lane and block of 64 rows, every wavefront taking every fourth
+    // slice (of eight wavefronts, four per half of the row blocks), four slices in flight per block.  The first batch is
+    // fetched here, ahead of the query rows and the first tiles, so that the wait for it includes neither.
+    constexpr int RBW = NW == 8 ? RW / 2 : RW;
+    const int rb0 = NW == 8 ? (wave >> 2) * RBW : 0, w4 = wave & 3;
+    int64_t srow[RBW];
+    float2 st0[RBW][4];
+    auto stats_load = [&](int s0, int64_t row, float2 (&st)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            st[u] = *reinterpret_cast<const float2*>(a.part_stats + ((int64_t)min(s0 + 4 * u, a.n_cmp_chunks - 1) * a.rows_total + row) * 2);
+    };
+    auto load_stats = [&](auto query_of, int nq) {
+#pragma unroll
+        for (int i = 0; i < RBW; ++i) {
+            const int rr = (rb0 + i) * kImpRows + lane;
+            const int j = rr / a.H_g;
+            srow[i] = ((int64_t)b * a.T + query_of(j < nq ? j : 0)) * a.H + g * a.H_g + rr % a.H_g;
+            stats_load(w4, srow[i], st0[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
     if (!a.share) {
         const auto query_of = [&](int j) { return qg * a.C + j; };
+        load_stats(query_of, min(a.C, a.T - qg * a.C));
         load_q(query_of, min(a.C, a.T - qg * a.C));
     }
-    const SeqMeta sm = build_tree_meta(tid, b, a.T, a.seq_lens, a.n_query, a.n_cmp, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth,
-                                       s_cmax, s_anc);
+    const SeqMeta sm = build_tree_meta(tid, mf, b, a.T, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth, s_cmax, s_anc);
     const int Tq = sm.Tq;
     const int n_routed = a.share ? (Tq + a.share - 1) / a.share : Tq;
     const int nq_grp = min(a.C, n_routed - qg * a.C);
@@ -539,38 +564,24 @@ k_importance32(const ImportanceArgs a) {
 
     // Tiles of 64 compressed rows, rows past the last one repeating it (their probabilities are masked by the
     // visibility limit), two tiles ahead of the one in use.
-    const __amdgpu_buffer_rsrc_t krsrc = Loader::make_rsrc(a.kc + b * a.kc_s[0] + g * a.kc_s[1], (int64_t)sm.n_cmp * a.kc_s[2]);
+    const u32x4 krsrc = Loader::make_rsrc(a.kc + b * a.kc_s[0] + g * a.kc_s[1], (int64_t)sm.n_cmp * a.kc_s[2]);
     const uint32_t krow = (uint32_t)a.kc_s[2];
     Loader kdir;
     kdir.init(krow, tid);
     auto issue_tile = [&](int tile) {
         kdir.issue(krsrc, (uint32_t)(tile * kTile) * krow, smem + ((tile - t0) % DEPTH) * TILE, krow, min(kTile, sm.n_cmp - tile * kTile), tid);
     };
+    if (a.share) load_stats([&](int j) { return s_qi[j]; }, nq_grp);
     issue_tile(t0);
     if (t0 + 1 < t1) issue_tile(t0 + 1);
-    if (a.share) {
-        const auto query_of = [&](int j) { return s_qi[j]; };
-        load_q(query_of, nq_grp);
-    }
+    if (a.share) load_q([&](int j) { return s_qi[j]; }, nq_grp);
 
-    // merged statistics of every row of this workgroup: M = max_s m_s, Z = sum_s Z_s 2^(m_s - M); one row per lane and
-    // block of 64 rows, every wavefront taking every fourth slice, four slices in flight
+    // merged statistics of every row of this workgroup: M = max_s m_s, Z = sum_s Z_s 2^(m_s - M)
     const int rows_wg = nq_grp * a.H_g;
 #pragma unroll
-    for (int rb = 0; rb < RW; ++rb) {
-        const int rr = rb * kImpRows + lane;
-        const int j = rr / a.H_g;
-        const int q_of_row = j < nq_grp ? s_qi[j] : s_qi[0];
-        const int64_t srow = ((int64_t)b * a.T + q_of_row) * a.H + g * a.H_g + rr % a.H_g;
+    for (int i = 0; i < RBW; ++i) {
         float M = -INFINITY, Z = 0.f;
-        if (wave >= 4) continue;      // (the first four wavefronts do this part, in the same order whatever NW is)
-        for (int s0 = wave; s0 < a.n_cmp_chunks; s0 += 16) {
-            float2 st[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int sl = min(s0 + 4 * u, a.n_cmp_chunks - 1);
-                st[u] = *reinterpret_cast<const float2*>(a.part_stats + ((int64_t)sl * a.rows_total + srow) * 2);
-            }
+        auto merge4 = [&](int s0, const float2 (&st)[4]) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if (s0 + 4 * u < a.n_cmp_chunks && st[u].y > 0.f) {
@@ -579,8 +590,14 @@ k_importance32(const ImportanceArgs a) {
                     M = Mn;
                 }
             }
+        };
+        merge4(w4, st0[i]);
+        for (int s0 = w4 + 16; s0 < a.n_cmp_chunks; s0 += 16) {
+            float2 st[4];
+            stats_load(s0, srow[i], st);
+            merge4(s0, st);
         }
-        s_part[wave * WGR + rr] = make_float2(M, Z);
+        s_part[w4 * WGR + (rb0 + i) * kImpRows + lane] = make_float2(M, Z);
     }
     __syncthreads();
     if (wave < RW) {          // wavefront w finishes row block w
@@ -645,26 +662,40 @@ k_importance32(const ImportanceArgs a) {
 
     // The 32 x 32 blocks of one key tile, one per row tile of this wavefront: 16 scores per lane and block; every K
     // fragment read from LDS serves all RTW row tiles.  Then, per block: exponentials, head sums and stores.
-    auto blocks_scores = [&](const char* tile_base, int kt, f32x16 (&s)[RTW]) {
+    // Issue order, pinned: LEAD fragment reads ahead of their matrix instructions (left to itself the compiler reads each
+    // fragment right before its instruction, and every one of them waits out the LDS latency); between the matrix
+    // instructions of a step and those of the next, `between(step)`.
+    constexpr int LEAD = STEPS < 6 ? STEPS : (RTW == 2 ? 3 : NW == 8 ? 4 : 6);
+    auto blocks_scores = [&](const char* tile_base, int kt, f32x16 (&s)[RTW], auto&& between) {
 #pragma unroll
         for (int t = 0; t < RTW; ++t)
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[t][i] = 0.f;
         const char* kb = tile_base + kt * 32 * Cfg::KROW;
+        auto k_frag = [&](int st) { return lds_read16(kb + koff[st & 3] + (st >> 2) * 128); };
+        u32x4 kf[LEAD];
+#pragma unroll
+        for (int st = 0; st < LEAD; ++st) kf[st] = k_frag(st);
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
-            const u32x4 kf = lds_read16(kb + koff[st & 3] + (st >> 2) * 128);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < RTW; ++t)
-                s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qf[t][st]), __builtin_bit_cast(bf16x8, kf), s[t], 0, 0, 0);
+                s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, qf[t][st]), __builtin_bit_cast(bf16x8, kf[st % LEAD]), s[t], 0, 0, 0);
+            if (st + LEAD < STEPS) kf[st % LEAD] = k_frag(st + LEAD);
+            between(st);
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto block_finish = [&](int tile, int kt, int t, const f32x16& s) {
+    // probabilities of elements [lo, hi) of a block, in place
+    auto block_exps = [&](int t, f32x16& s, int lo, int hi) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (i >= lo && i < hi) s[i] = fast_exp2(__builtin_fmaf(s[i], a.scale_log2, -rowMp[t][i]));
+    };
+    auto block_finish = [&](int tile, int kt, int t, const f32x16& p) {      // p: probabilities
         const int c = tile * kTile + 32 * kt + n;
         float hs[4];                 // sums of this lane's four consecutive rows 8 j + 4 hb + 0..3
-        float p[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) p[i] = fast_exp2(__builtin_fmaf(s[i], a.scale_log2, -rowMp[t][i]));
 #pragma unroll
         for (int j = 0; j < 4; ++j) hs[j] = (p[4 * j] + p[4 * j + 1]) + (p[4 * j + 2] + p[4 * j + 3]);
         if constexpr (HGM == 16) {
@@ -707,12 +738,16 @@ k_importance32(const ImportanceArgs a) {
     // store instructions per block that are issued for certain (one whose predicate is false in every lane may or may
     // not be issued: it is not counted; counting too few only makes the waits below longer)
     int ns_step = 0;
+    constexpr int NS_FULL = HGM >= 4 ? KTW * RTW * QPT : 0;
     if constexpr (HGM >= 4) {
 #pragma unroll
         for (int t = 0; t < RTW; ++t)
 #pragma unroll
             for (int u = 0; u < QPT; ++u) ns_step += KTW * (__builtin_amdgcn_ballot_w64(rowQ[t][u] >= 0) != 0ull);
     }
+
+#pragma unroll
+    for (int t = 0; t < RTW; ++t) arrived(qf[t]);        // (not with the third tile, which the first step issues)
 
     // Software pipeline over the tiles of the slice.  Step `tile`: wait for the loads this wavefront issued for it
     // (younger operations on the in-order counter: the LD loads of the next tile and the stores of the two steps
@@ -722,22 +757,31 @@ k_importance32(const ImportanceArgs a) {
     for (int tile = t0; tile < t1; ++tile) {
         if (tile + 1 >= t1) wait_vmcnt<0>();
         else if (tile - t0 < 2) wait_vmcnt<LD>();
+        else if (ns_step == NS_FULL) wait_vmcnt<LD + 2 * NS_FULL>();     // (every store has a query: all but the last group's)
         else wait_vmcnt_upto(LD + 2 * ns_step);
         __syncthreads();
         if (tile + 2 < t1) issue_tile(tile + 2);
         __builtin_amdgcn_sched_barrier(0);
         const char* tb = smem + ((tile - t0) % DEPTH) * TILE;
-        f32x16 s_cur[RTW], s_next[RTW];
-        blocks_scores(tb, kt0, s_cur);
+        f32x16 s_cur[RTW];
+        if constexpr (NW == 8 || KTW == 1) {
 #pragma unroll
-        for (int k = 0; k < KTW; ++k) {
-            if (k + 1 < KTW) blocks_scores(tb, kt0 + k + 1, s_next);
+            for (int k = 0; k < KTW; ++k) {
+                blocks_scores(tb, kt0 + k, s_cur, [](int) {});
 #pragma unroll
-            for (int t = 0; t < RTW; ++t) block_finish(tile, kt0 + k, t, s_cur[t]);
-            if (k + 1 < KTW) {
-#pragma unroll
-                for (int t = 0; t < RTW; ++t) s_cur[t] = s_next[t];
+                for (int t = 0; t < RTW; ++t) { block_exps(t, s_cur[t], 0, 16); block_finish(tile, kt0 + k, t, s_cur[t]); }
             }
+        } else {
+            f32x16 s_next[RTW];
+            blocks_scores(tb, kt0, s_cur, [](int) {});
+            blocks_scores(tb, kt0 + 1, s_next, [&](int st) {
+#pragma unroll
+                for (int t = 0; t < RTW; ++t) block_exps(t, s_cur[t], st * 16 / STEPS, (st + 1) * 16 / STEPS);
+            });
+#pragma unroll
+            for (int t = 0; t < RTW; ++t) block_finish(tile, kt0, t, s_cur[t]);
+#pragma unroll
+            for (int t = 0; t < RTW; ++t) { block_exps(t, s_next[t], 0, 16); block_finish(tile, kt0 + 1, t, s_next[t]); }
         }
     }
 }

@@ -9,9 +9,17 @@
 //   the B operand of O^T = V^T P^T.
 //
 //   K and V tiles of 64 compressed rows go from global memory straight into a ring of three LDS stages, with bank
-//   swizzles chosen through the per-lane global addresses, two tiles ahead of the one in use; one barrier per tile.
-//   Every tile reaches LDS once per 256 rows.  The two wavefronts of a SIMD overlap each other's matrix and vector
-//   phases (products, softmax arithmetic, P.V).
+//   swizzles chosen through the per-lane global addresses, two tiles ahead of the one in use.  Every tile reaches LDS
+//   once per 256 rows.
+//
+//   A tile is a matrix phase (P.V of the tile before, then this tile's products: 40 matrix instructions at d_k = 192)
+//   and a vector phase (softmax, and the loads of a later tile).  The eight wavefronts run in two halves, one phase apart,
+//   with a barrier after every phase: of the two wavefronts of a SIMD one is always in its matrix phase while the other is
+//   in its vector phase.  (All in step, both wanted the same pipe at the same time, the loads held all eight up, and the
+//   compiler waited for the loads in flight before every P.V.)  4 sequences of 40 queries over 128K tokens: a tile takes
+//   4030 clocks instead of 5400, of which the matrix instructions are 2560; as both pipes work at once the clock falls from
+//   2.37 to 1.93 GHz, so that the launch gains less than that, 69.5 -> 66 us (a stream of these matrix instructions alone,
+//   on random data, runs at 1.65 GHz).  With 16 queries per sequence a tile is used once and the launch is at 4.3 TB/s.
 //
 //   The running maximum is a reference that is only raised when a tile's maximum exceeds it by more than 2^8
 //   (probabilities stay below 256: exact in the partial state's own terms, which carries the reference), so the
@@ -26,6 +34,8 @@
 //
 // Output: one partial softmax state per row and slice, in the format of the streaming kernel (k_stream.hpp).
 #pragma once
+#include <type_traits>
+
 #include "k_stream.hpp"
 #include "work_table.hpp"
 
@@ -82,7 +92,9 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
     extern __shared__ __align__(16) char smem[];
     __shared__ AncSet s_anc[kMaxT];
     __shared__ int s_par[kMaxT], s_depth[kMaxT], s_cmax[kMaxT];
-    __shared__ int s_pref[kScan32MaxBalancedB + 1], s_wsum[kScan32Threads / 64];     // balanced split
+    // balanced split: cost prefix and the lengths of every sequence (fetched once, in one round trip)
+    __shared__ int s_pref[BAL ? kScan32MaxBalancedB + 1 : 1], s_wsum[kScan32Threads / 64];
+    __shared__ int s_len[BAL ? kScan32MaxBalancedB : 1], s_nq[BAL ? kScan32MaxBalancedB : 1], s_nc[BAL ? kScan32MaxBalancedB : 1];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hb = lane >> 5;
@@ -96,8 +108,6 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
     const uint32_t krow = (uint32_t)a.kc_s[2], vrow = (uint32_t)a.vc_s[2];
     KLoader kld;
     VLoader vld;
-    kld.init(krow, tid);
-    vld.init(vrow, tid);
     // this lane's byte offsets into a K tile for the four contraction steps of a 128-byte group: key row n of a
     // 32-key block, granule 2 q + hb, swizzled with bits 1..3 of the row
     int koff[4];
@@ -111,6 +121,7 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) voff[mb] = r * VROW + VLoader::swizzled(r, 4 * mb + 2 * mh) * 16 + (p & 3) * 8;
     }
+    const bool late = __builtin_amdgcn_readfirstlane(wave) >= 4;      // the half that runs one phase behind
     const int rr = wave * 32 + n;           // row of the workgroup
     const int jrow = rr / a.H_g;            // its verifier query within the group
     const float raise = kScan32RaiseLog2 / a.scale_log2;     // in raw score units
@@ -124,12 +135,20 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
     int x = 0, x_end = 1, range_len = 1, range_id = 0, b_cur = 0;
     const int pc = a.pair_cost;
     if constexpr (BAL) {
-        auto cost_of = [&](int bb) {
-            if (bb >= a.B) return 0;
-            const int tq = a.n_query ? min(max(a.n_query[bb], 0), a.T) : a.T;
-            return tq > 0 ? pc + max(1, (min(max(a.n_cmp[bb], 0), a.max_n_cmp) + kTile - 1) / kTile) : 0;
-        };
-        const int n0 = cost_of(2 * tid), n1 = cost_of(2 * tid + 1);
+        int cost[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int bb = 2 * tid + i;
+            cost[i] = 0;
+            if (bb < a.B) {
+                const int len = a.seq_lens[bb], nc = a.n_cmp[bb], nq = a.n_query ? a.n_query[bb] : a.T;
+                s_len[bb] = len;
+                s_nc[bb] = nc;
+                s_nq[bb] = nq;
+                if (nq > 0) cost[i] = pc + max(1, (min(max(nc, 0), a.max_n_cmp) + kTile - 1) / kTile);
+            }
+        }
+        const int n0 = cost[0], n1 = cost[1];
         int incl = n0 + n1;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -210,6 +229,13 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
         // ---- B operands of S^T = K Q^T: row n of this wavefront's block of 32 rows, all contraction steps.  The address
         //      needs nothing from the sequence's metadata, so the loads go first (queries past the sequence's count exist in
         //      the buffer; rows that do not exist are zeroed below)
+        MetaFetch mf{};
+        const bool new_meta = !BAL || b != b_meta;      // (uniform) the next KV head of the same sequence keeps the metadata
+        if constexpr (BAL) {
+            if (new_meta) mf = MetaFetch{s_len[b], s_nq[b], s_nc[b]};
+        } else {
+            mf = fetch_tree_meta(b, a.T, a.seq_lens, a.n_query, a.n_cmp);
+        }
         u32x4 qf[STEPS];
         {
             const int qi = min(qg * a.C + jrow, a.T - 1);
@@ -218,9 +244,8 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
             for (int st = 0; st < STEPS; ++st) qf[st] = *reinterpret_cast<const u32x4*>(qp + st * 32);
         }
 
-        if (!BAL || b != b_meta) {      // (uniform) the next KV head of the same sequence keeps the metadata
-            sm = build_tree_meta(tid, b, a.T, a.seq_lens, a.n_query, a.n_cmp, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth,
-                                 s_cmax, s_anc);
+        if (new_meta) {
+            sm = build_tree_meta(tid, mf, b, a.T, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth, s_cmax, s_anc);
             b_meta = b;
         }
         const int nq_grp = min(a.C, sm.Tq - qg * a.C);    // verifier queries of this group that exist
@@ -252,14 +277,22 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
         }
 
         // ---- tile loads: stage t = {K(t), V(t)} lives in slot (t - t0) % 3
-        const __amdgpu_buffer_rsrc_t krsrc = KLoader::make_rsrc(a.kc + b * a.kc_s[0] + g * a.kc_s[1], (int64_t)sm.n_cmp * a.kc_s[2]);
-        const __amdgpu_buffer_rsrc_t vrsrc = VLoader::make_rsrc(a.vc + b * a.vc_s[0] + g * a.vc_s[1], (int64_t)sm.n_cmp * a.vc_s[2]);
+        const u32x4 krsrc = KLoader::make_rsrc(a.kc + b * a.kc_s[0] + g * a.kc_s[1], (int64_t)sm.n_cmp * a.kc_s[2]);
+        const u32x4 vrsrc = VLoader::make_rsrc(a.vc + b * a.vc_s[0] + g * a.vc_s[1], (int64_t)sm.n_cmp * a.vc_s[2]);
+        kld.init(krow, tid);
+        vld.init(vrow, tid);
         auto stage_of = [&](int t) { return smem + ((t - t0) % 3) * STAGE; };
-        auto issue_stage = [&](int t) {
-            const int rows = min(kTile, sm.n_cmp - t * kTile);
-            kld.template issue<true>(krsrc, (uint32_t)(t * kTile) * krow, stage_of(t), krow, rows, tid);
-            vld.template issue<true>(vrsrc, (uint32_t)(t * kTile) * vrow, stage_of(t) + KT, vrow, rows, tid);
+        // K(t) and V(t), by loads of KI and VI instructions; past the slice's last tile the same instructions with an empty
+        // buffer, which fetch nothing (the counted waits below need no cases, the matrix phases no branches)
+        auto rsrc_of = [&](u32x4 r, int t) { return u32x4{r[0], r[1], t < t1 ? r[2] : 0u, r[3]}; };
+        auto prepare_k = [&](int t) {
+            if (t < t1 && sm.n_cmp - t * kTile < kTile) kld.clamp(krow, sm.n_cmp - t * kTile, tid);     // (uniform; a sequence's last tile)
         };
+        auto prepare_v = [&](int t) {
+            if (t < t1 && sm.n_cmp - t * kTile < kTile) vld.clamp(vrow, sm.n_cmp - t * kTile, tid);
+        };
+        auto load_k = [&](int t, int j) { kld.issue_one(j, rsrc_of(krsrc, t), (uint32_t)(t < t1 ? t * kTile : 0) * krow, stage_of(t), tid); };
+        auto load_v = [&](int t, int j) { vld.issue_one(j, rsrc_of(vrsrc, t), (uint32_t)(t < t1 ? t * kTile : 0) * vrow, stage_of(t) + KT, tid); };
 
         f32x16 acc[MB];
 #pragma unroll
@@ -267,49 +300,83 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[mb][i] = 0.f;
         float mref = -INFINITY, zrun = 0.f;
+        f32x16 s[2];            // scores of a tile, between its matrix phase and its vector phase
+        u32x4 pk[2][2];         // its probabilities, between the vector phase and the next matrix phase
 
-        if (t0 < t1) {
-            issue_stage(t0);
-            if (t0 + 1 < t1) issue_stage(t0 + 1);
-        }
-        for (int tile = t0; tile < t1; ++tile) {
-            // Loads complete in issue order: stage `tile` has landed when no more loads are outstanding than the next
-            // stage holds (stage tile + 2 is issued after this wait).
-            if (tile + 1 < t1) wait_vmcnt<KI + VI>();
-            else wait_vmcnt<0>();
-            __syncthreads();        // stage `tile` is in LDS; every wavefront has left stage tile - 1
-            if (tile + 2 < t1) issue_stage(tile + 2);
+        // Between two phases.  Into the even phase of tile t: K(t) and V(t - 1) have landed (they were issued two tiles ago;
+        // loads complete in issue order, and only K(t + 1) and V(t) were issued since), and every wavefront has left
+        // K(t - 1) and V(t - 2), whose places the matrix phase of tile t fills with K(t + 2) and V(t + 1).
+        auto boundary = [&](bool into_even) {
+            if (into_even) wait_vmcnt<KI + VI>();
+            __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
+        };
+        // The loads of tile t's even phase.  They are issued by the half that is in its vector phase: the vector memory pipe
+        // takes 64 B per clock, so the 20 instructions of a phase take 330 clocks, which a matrix phase would spend waiting.
+        auto issue_ahead = [&](int t) {
+            prepare_k(t + 2);
+            prepare_v(t + 1);
+#pragma unroll
+            for (int j = 0; j < KI; ++j) load_k(t + 2, j);
+#pragma unroll
+            for (int j = 0; j < VI; ++j) load_v(t + 1, j);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // Matrix phase: O^T += V(tile - 1)^T P^T (not for the first tile), then S^T = K(tile) Q^T (not behind the last one).
+        // One stream of fragments, its order pinned: LEAD fragment reads ahead of their matrix instructions, so that the LDS
+        // latency of every fragment is covered by the instructions of the fragments before it.
+        //   accumulation, fragment i: 32 columns of V (block i % MB) against keys 16 (i / MB) .. + 15, read transposed from the
+        //     row-major tile (two 8-byte reads: keys 4 hb .. + 3 and 8 + 4 hb .. + 3 of the run, the order of the probabilities in pk)
+        //   products, fragment i: contraction step i / 2 of key block i % 2.  s[kb] = keys 32 kb .. + 31 against this wavefront's
+        //     rows; lane layout: row n of the block, keys 32 kb + 8 j + 4 hb + r at vector index 4 j + r
+        auto matrix_phase = [&](auto first, int tile) {
+            constexpr int N_V = decltype(first)::value ? 0 : 4 * MB, N = N_V + 2 * STEPS;
+            constexpr int LEAD = 6;
             const char* kt = stage_of(tile);
-            const char* vt = kt + KT;
-
-            // ---- S^T: s[kb] = keys 32 kb .. + 31 against this wavefront's rows; two independent accumulator chains.
-            //      Lane layout: row n of the block, keys 32 kb + 8 j + 4 hb + r at vector index 4 j + r
-            f32x16 s[2];
+            const char* vt = stage_of(tile - 1 + (decltype(first)::value ? 1 : 0)) + KT;
+            auto frag = [&](int i) {
+                if (i < N_V) {
+                    const int kh = i / MB, mb = i % MB;
+                    const u32x2 v0 = lds_read_tr16(vt + voff[mb] + (16 * kh) * VROW);
+                    const u32x2 v1 = lds_read_tr16(vt + voff[mb] + (16 * kh + 8) * VROW);
+                    return u32x4{v0[0], v0[1], v1[0], v1[1]};
+                }
+                const int st = (i - N_V) >> 1, kb = (i - N_V) & 1;
+                return lds_read16(kt + kb * 32 * KROW + koff[st & 3] + (st >> 2) * 128);
+            };
+            // Above the other half's vector phase: between two wavefronts that both have vector instructions the older one goes
+            // first, and the first LDS addresses of a younger one would wait for the whole phase of the older.
+            __builtin_amdgcn_s_setprio(1);
+            u32x4 fb[LEAD];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < LEAD; ++i) fb[i] = frag(i);
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
-            {
-                // issue order, pinned: LEAD fragment reads ahead of their matrix instructions, so that the LDS latency of
-                // every fragment is covered by the instructions of the fragments before it
-                constexpr int N_RD = 2 * STEPS, LEAD = 6;
-                auto k_frag = [&](int i) {      // fragment i: contraction step i / 2 of key block i % 2
-                    const int st = i >> 1, kb = i & 1;
-                    return lds_read16(kt + kb * 32 * KROW + koff[st & 3] + (st >> 2) * 128);
-                };
-                u32x4 kfb[LEAD];
 #pragma unroll
-                for (int i = 0; i < LEAD; ++i) kfb[i] = k_frag(i);
-#pragma unroll
-                for (int i = 0; i < N_RD; ++i) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kfb[i % LEAD]), __builtin_bit_cast(bf16x8, qf[i >> 1]),
-                                                                      s[i & 1], 0, 0, 0);
-                    if (i + LEAD < N_RD) kfb[i % LEAD] = k_frag(i + LEAD);
-                }
+            for (int i = 0; i < N; ++i) {
                 __builtin_amdgcn_sched_barrier(0);
+                if (N_V && i == N_V && tile >= t1) break;      // (uniform)
+                if (i < N_V) {
+                    const int kh = i / MB, mb = i % MB;
+                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[i % LEAD]), __builtin_bit_cast(bf16x8, pk[kh >> 1][kh & 1]),
+                                                                      acc[mb], 0, 0, 0);
+                } else {
+                    const int st = (i - N_V) >> 1, kb = (i - N_V) & 1;
+                    s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[i % LEAD]), __builtin_bit_cast(bf16x8, qf[st]),
+                                                                    s[kb], 0, 0, 0);
+                }
+                if (i + LEAD < N) fb[i % LEAD] = frag(i + LEAD);
             }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+        };
+        // ---- softmax step in the log2 domain: raise the reference if needed, scores -> bf16 probabilities (B operands:
+        //      pk[kb][h] = keys 32 kb + 16 h .. + 15 in the order the products delivered them)
+        auto softmax = [&](int tile) {
+            issue_ahead(late ? tile + 1 : tile);
             if (tile >= tf) {       // (uniform) visibility limits: keys at or beyond the row's limit become -inf
                 const int lim = cmaxr - tile * kTile - 4 * hb;     // keys with 32 kb + 8 j + r < lim are visible
 #pragma unroll
@@ -318,8 +385,6 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
                     for (int i = 0; i < 16; ++i)
                         if (32 * kb + 8 * (i >> 2) + (i & 3) >= lim) s[kb][i] = -INFINITY;
             }
-            // ---- softmax step in the log2 domain: raise the reference if needed, scores -> bf16 probabilities (B operands:
-            //      pk[kb][h] = keys 32 kb + 16 h .. + 15 in the order the products delivered them)
             float mx = max_nan(s[0][0], s[1][0]);
 #pragma unroll
             for (int i = 1; i < 16; ++i) mx = max_nan(mx, max_nan(s[0][i], s[1][i]));
@@ -330,7 +395,6 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
             const float alpha = up ? fast_exp2((mref - m_use) * a.scale_log2) : 1.f;
             const float neg_ms = -m_use * a.scale_log2;
             float rs4[4] = {0.f, 0.f, 0.f, 0.f};      // four independent chains
-            u32x4 pk[2][2];
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
                 float p[16];
@@ -356,30 +420,39 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
 #pragma unroll
                     for (int i = 0; i < 16; ++i) acc[mb][i] *= alpha;
             }
-            // ---- O^T += V^T P^T: A operand = 32 columns of V against 16 keys, read transposed from the row-major tile (two
-            //      8-byte reads: keys 4 hb .. + 3 and 8 + 4 hb .. + 3 of the run, the order of the probabilities in pk)
-            {
-                constexpr int N_F = 4 * MB, LEAD = 4;       // fragment i: keys 16 (i / MB) .. + 15 against column block i % MB
-                auto v_frag = [&](int i) {
-                    const int kh = i / MB, mb = i % MB;
-                    const u32x2 v0 = lds_read_tr16(vt + voff[mb] + (16 * kh) * VROW);
-                    const u32x2 v1 = lds_read_tr16(vt + voff[mb] + (16 * kh + 8) * VROW);
-                    return u32x4{v0[0], v0[1], v1[0], v1[1]};
-                };
-                u32x4 vfb[LEAD];
-                __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" : "+v"(pk[0][0]), "+v"(pk[0][1]), "+v"(pk[1][0]), "+v"(pk[1][1]));     // (the conversions belong to this phase)
+            __builtin_amdgcn_sched_barrier(0);
+        };
+
+        if (t0 < t1) {
+            // the first matrix phase waits for the query rows and K(t0) only
+            prepare_k(t0);
 #pragma unroll
-                for (int i = 0; i < LEAD; ++i) vfb[i] = v_frag(i);
+            for (int j = 0; j < KI; ++j) load_k(t0, j);
+            arrived(qf);
+            wait_vmcnt<0>();
+            __syncthreads();
+            prepare_k(t0 + 1);
 #pragma unroll
-                for (int i = 0; i < N_F; ++i) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    const int kh = i / MB, mb = i % MB;
-                    acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vfb[i % LEAD]), __builtin_bit_cast(bf16x8, pk[kh >> 1][kh & 1]),
-                                                                      acc[mb], 0, 0, 0);
-                    if (i + LEAD < N_F) vfb[i % LEAD] = v_frag(i + LEAD);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+            for (int j = 0; j < KI; ++j) load_k(t0 + 1, j);
+            prepare_v(t0);
+#pragma unroll
+            for (int j = 0; j < VI; ++j) load_v(t0, j);
+            __builtin_amdgcn_sched_barrier(0);
+            if (late) {
+                issue_ahead(t0);
+                boundary(false);
             }
+            matrix_phase(std::true_type{}, t0);
+            for (int tile = t0;; ++tile) {
+                boundary(late);
+                softmax(tile);
+                boundary(!late);
+                matrix_phase(std::false_type{}, tile + 1);
+                if (tile + 1 == t1) break;
+            }
+            if (!late) boundary(false);
+            wait_vmcnt<0>();        // (the empty loads count too)
         }
 
         // ---- partial state of this slice: (reference maximum, Z) per row and the un-normalised accumulator; lane layout of

@@ -116,6 +116,7 @@ constexpr int kRolesCmp = 1, kRolesWin = 2, kRolesCmpWin = 3, kRolesSlc = 4, kRo
 
 template <bool BF16, int DK, int DV, int NRT, int ROLES>
 __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) k_stream(const StreamArgs a) {
+    if constexpr (NRT == 1 && ROLES != kRolesAll) touch_args<StreamArgs>();
     using Cfg = StreamCfg<BF16, DK, DV>;
     constexpr int ES = Cfg::ES, KROWB = Cfg::KROW, KCH = Cfg::KCH, VP = Cfg::VP, VR = Cfg::VR, MT = Cfg::MT;
     extern __shared__ __align__(16) char smem[];
@@ -185,6 +186,7 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
     //      nothing from the sequence's metadata, so the loads go first and overlap the latency of everything below
     //      (rows past the sequence's query count exist in the buffer; their fragments are zeroed once the count is known)
     //      (two row tiles per wave: the registers do not allow it; those launches are long, the loads follow the metadata)
+    const MetaFetch mf = fetch_tree_meta(b, a.T, a.seq_lens, a.n_query, a.n_cmp);
     u32x4 qf[NRT][KCH];
     if constexpr (NRT == 1) {
         const int rr = wave * 16 + n;
@@ -200,9 +202,7 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
             pre_id = a.sel_idx[(((int64_t)b * a.T + qg * a.C + tid / a.n_sel) * a.H_kv + g) * a.n_sel + tid % a.n_sel];
     }
 
-    const SeqMeta sm = build_tree_meta(tid, b, a.T, a.seq_lens, a.n_query, a.n_cmp, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth,
-                                       s_cmax,
-                                       s_anc);
+    const SeqMeta sm = build_tree_meta(tid, mf, b, a.T, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth, s_cmax, s_anc);
     const int L = sm.L, Tq = sm.Tq;
     const int nq_grp = min(a.C, Tq - qg * a.C);   // verifier queries of this group that exist
     const int n_slots_kv = L + Tq;                // raw KV rows that exist for this sequence
@@ -371,7 +371,7 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
     // barriers per tile separate the LDS writes from the fragment reads.  Measured with in-kernel clocks, the
     // prefetched loads have nearly always arrived by the time they are needed at one tile ahead.
     constexpr int AHEAD = 1;
-    const __amdgpu_buffer_rsrc_t krsrc = DirectRowTile<Cfg::KROW>::make_rsrc(kbase, (int64_t)max(rows_exist, 0) * krow);
+    const u32x4 krsrc = DirectRowTile<Cfg::KROW>::make_rsrc(kbase, (int64_t)max(rows_exist, 0) * krow);
     DirectRowTile<Cfg::KROW> kdir;
     TransposedTileRegs<BF16, DV> vregs[AHEAD];
     auto tile_of = [&](int it) { return r_slc ? s_id[it] : it; };

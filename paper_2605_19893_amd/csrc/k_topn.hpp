@@ -278,9 +278,8 @@ __global__ void __launch_bounds__(kThreads, 8) k_topn(const TopnArgs a) {
     const int x = (blockIdx.x / a.H_kv) % a.T;
     const int b = blockIdx.x / (a.H_kv * a.T);
 
-    const SeqMeta sm = build_tree_meta(tid, b, a.T, a.seq_lens, a.n_query, a.n_cmp, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth,
-                                       s_cmax,
-                                       s_anc);
+    const MetaFetch mf = fetch_tree_meta(b, a.T, a.seq_lens, a.n_query, a.n_cmp);
+    const SeqMeta sm = build_tree_meta(tid, mf, b, a.T, a.parents, a.l, a.d, a.max_seq_len, a.max_n_cmp, s_par, s_depth, s_cmax, s_anc);
     if (x >= sm.Tq) {
         if (tid < a.n_sel) a.sel_idx[(((int64_t)b * a.T + x) * a.H_kv + g) * a.n_sel + tid] = -1;
         return;

@@ -81,8 +81,9 @@ __device__ __forceinline__ void block_build_work_table(const int (&tiles)[PT], i
 
 // item -> (sequence, slice, slices); false: the table has fewer items
 __device__ __forceinline__ bool work_table_item(const int32_t* table, int item, int B, int& b, int& part, int& parts) {
-    if (item >= table[0]) return false;
-    const int4 e = reinterpret_cast<const int4*>(table + kWorkTableHeader)[item];
+    const int n = table[0];
+    const int4 e = reinterpret_cast<const int4*>(table + kWorkTableHeader)[item];     // (the table has room for every item asked for)
+    if (item >= n) return false;
     b = min(max(e.x, 0), B - 1);
     part = e.y;
     parts = e.z;
