@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_e
                 } else {
                     // the approximate shared-index variant selects for the representative of the query's sharing group
                     const int i = a.share ? group_representative(s_depth, (x / a.share) * a.share, min((x / a.share + 1) * a.share, Tq)) : x;
-                    wave_topn(a.colsum + (((int64_t)b * a.T + i) * a.H_kv + g) * a.nc_pitch, min(s_cmax[i], a.nc_pitch),
+                    wave_topn<(DK > 64)>(a.colsum + (((int64_t)b * a.T + i) * a.H_kv + g) * a.nc_pitch, min(s_cmax[i], a.nc_pitch),
                               min((L + i) / a.l_sel, a.max_blocks - 1), a.l, a.d, a.l_sel, a.n_sel, a.n_init, a.n_local, ws, lane, out);
                 }
                 wave_lds_sync();

@@ -18,6 +18,8 @@
 // plain serial argmax over LDS takes over.  LDS keeps the importances as their 32-bit patterns (the index is the position;
 // keys are composed on the fly): 18 KB at 2048 blocks, eight workgroups per CU.
 #pragma once
+#include <type_traits>
+
 #include "device_common.hpp"
 
 namespace ssv {
@@ -87,52 +89,90 @@ __device__ __forceinline__ uint64_t topn_key(uint32_t bits, int j) {
 }
 
 // cs: colsum row of the (representative) query; ncv: its visible compressed rows; J: block of its own slot.
-// Writes the n_sel entries (ascending, -1 padding) to out[] (LDS or global).
+// Writes the n_sel entries (ascending, -1 padding) to out[] (LDS or global).  WIDE: 1024 blocks in flight instead of 512 (80
+// registers; not where they would cost the caller's third workgroup per CU, at d = 64).
+template <bool WIDE>
 __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l, int d, int l_sel, int n_sel, int n_init,
                                           int n_local, const WaveTopnScratch& w, int lane, int32_t* out) {
     const int a_ratio = l_sel / d, b_ratio = l / d;
     const int n_eff = min(n_sel, J + 1);
     const int n_terms = a_ratio + b_ratio - 1;
     const int j_last_scored = J - max(n_local, 0);
-    uint64_t best = 0;
+    uint32_t best = 0;         // largest importance among the blocks of this lane (index mod 64), as its bit pattern
     for (int j = max(j_last_scored + 1, 0); j <= J; ++j) {     // forced trailing local blocks, each with its owner lane
         if ((j & 63) != lane) continue;
         w.bits[j] = 0x7F800000u;
-        const uint64_t key = topn_key(0x7F800000u, j);
-        best = key > best ? key : best;
+        best = max(best, 0x7F800000u);
     }
     constexpr int NB = 4;     // blocks per lane whose column loads are issued together
     if (a_ratio == 4 && b_ratio == 2) {
-        // the standard geometry: block j takes columns 4j-1 .. 4j+3 with weights 1 2 2 2 1; one 16-byte and one
-        // 4-byte load per block, eight blocks per lane in flight (same terms in the same order as the general form)
-        constexpr int NF = 8;
-        for (int j0 = lane; j0 <= j_last_scored; j0 += 64 * NF) {
+        // The standard geometry: block j takes columns 4j-1 .. 4j+3 with weights 1 2 2 2 1; one 16-byte and one 4-byte load
+        // per block (same terms in the same order as the general form).  This is one wavefront on its SIMD, a vector
+        // instruction every five clocks: groups of 64 blocks whose columns are all visible take none for conditions, and up to
+        // 1024 blocks are in flight together.  (2048 blocks: 13 us of the selected launch of 40-node trees at 128K with the
+        // conditions at every block and 512 in flight.)
+        auto block_loads = [&](int j, f32x4& x, float& xm) {
+            const int c0 = j <= j_last_scored ? 4 * j : 0;
+            // (a row holds nc_pitch columns, a multiple of 64: a block starting past it has no visible column)
+            x = *reinterpret_cast<const f32x4*>(cs + (c0 < ncv ? c0 : 0));
+            xm = cs[(c0 >= 1 && c0 - 1 < ncv) ? c0 - 1 : 0];
+        };
+        auto put = [&](int j, float imp) {
+            const uint32_t bits = j < n_init ? 0x7F800000u : __float_as_uint(imp);
+            w.bits[j] = bits;
+            best = max(best, bits);
+        };
+        auto block_any = [&](int j, const f32x4& x, float xm) {
+            if (j > j_last_scored) return;
+            const int c0 = 4 * j;
+            float imp = 0.f;
+            if (c0 >= 1 && c0 - 1 < ncv) imp += 1.f * xm;
+            if (c0 < ncv) imp += 2.f * x[0];
+            if (c0 + 1 < ncv) imp += 2.f * x[1];
+            if (c0 + 2 < ncv) imp += 2.f * x[2];
+            if (c0 + 3 < ncv) imp += 1.f * x[3];
+            put(j, imp);
+        };
+        const int groups = min(j_last_scored + 1, ncv >> 2) >> 6;      // groups of 64 blocks with every column visible
+        constexpr int NR = 2;                                          // the remainder's loads go first (it rarely has more groups)
+        f32x4 rx[NR];
+        float rm[NR];
+#pragma unroll
+        for (int v = 0; v < NR; ++v) block_loads((groups + v) * 64 + lane, rx[v], rm[v]);
+        int last63 = 0;        // (uniform) column before the group's first one: the last column of lane 63 of the group before
+        auto full_groups = [&](auto nf, int g0) {
+            constexpr int NF = decltype(nf)::value;
             f32x4 x[NF];
-            float xm[NF];
+#pragma unroll
+            for (int v = 0; v < NF; ++v) x[v] = *reinterpret_cast<const f32x4*>(cs + 4 * (min(g0 + v, groups - 1) * 64 + lane));
+            // Past the last group: that group again (no branches: the loads would sink into them, behind each other).  The
+            // column before a block's own comes from the lane below, not from memory: its load would be as expensive as theirs.
 #pragma unroll
             for (int v = 0; v < NF; ++v) {
-                const int j = j0 + v * 64;
-                const int c0 = j <= j_last_scored ? 4 * j : 0;
-                // (a row holds nc_pitch columns, a multiple of 64: a block starting past it has no visible column)
-                x[v] = *reinterpret_cast<const f32x4*>(cs + (c0 < ncv ? c0 : 0));
-                xm[v] = cs[(c0 >= 1 && c0 - 1 < ncv) ? c0 - 1 : 0];
+                const int j = min(g0 + v, groups - 1) * 64 + lane;
+                const float xm = __int_as_float(__builtin_amdgcn_update_dpp(last63, __float_as_int(x[v][3]), 0x138, 0xf, 0xf, false));   // lane l: x[3] of l - 1
+                const float imp = (((xm + 2.f * x[v][0]) + 2.f * x[v][1]) + 2.f * x[v][2]) + x[v][3];
+                w.bits[j] = __float_as_uint(imp);
+                best = max(best, __float_as_uint(imp));
+                last63 = g0 + v + 1 < groups ? __builtin_amdgcn_readlane(__float_as_int(x[v][3]), 63) : last63;
             }
+        };
+        int g0 = 0;
+        if constexpr (WIDE) {
+            for (; groups - g0 > 8; g0 += 16) full_groups(std::integral_constant<int, 16>{}, g0);
+        }
+        for (; g0 < groups; g0 += 8) full_groups(std::integral_constant<int, 8>{}, g0);
+        if (groups > 0 && lane < n_init) {         // (n_init <= n_sel <= 32: forced blocks are in the first group)
+            w.bits[lane] = 0x7F800000u;
+            best = 0x7F800000u;
+        }
 #pragma unroll
-            for (int v = 0; v < NF; ++v) {
-                const int j = j0 + v * 64;
-                if (j > j_last_scored) continue;
-                const int c0 = 4 * j;
-                float imp = 0.f;
-                if (c0 >= 1 && c0 - 1 < ncv) imp += 1.f * xm[v];
-                if (c0 < ncv) imp += 2.f * x[v][0];
-                if (c0 + 1 < ncv) imp += 2.f * x[v][1];
-                if (c0 + 2 < ncv) imp += 2.f * x[v][2];
-                if (c0 + 3 < ncv) imp += 1.f * x[v][3];
-                const uint32_t bits = j < n_init ? 0x7F800000u : __float_as_uint(imp);
-                w.bits[j] = bits;
-                const uint64_t key = topn_key(bits, j);
-                best = key > best ? key : best;
-            }
+        for (int v = 0; v < NR; ++v) block_any((groups + v) * 64 + lane, rx[v], rm[v]);
+        for (int j = (groups + NR) * 64 + lane; j <= j_last_scored; j += 64) {
+            f32x4 x;
+            float xm;
+            block_loads(j, x, xm);
+            block_any(j, x, xm);
         }
     } else
     for (int j0 = lane; j0 <= j_last_scored; j0 += 64 * NB) {
@@ -174,8 +214,7 @@ __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l
             if (j <= j_last_scored) {
                 const uint32_t bits = j < n_init ? 0x7F800000u : __float_as_uint(imp[v]);
                 w.bits[j] = bits;
-                const uint64_t key = topn_key(bits, j);
-                best = key > best ? key : best;
+                best = max(best, bits);
             }
         }
     }
@@ -185,10 +224,9 @@ __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l
     // and with fewer than n_eff bests the threshold stays 0: every block is a candidate).
     uint32_t thr_bits = 0;
     {
-        const uint32_t mine = (uint32_t)(best >> 32);
         for (int bit = 30; bit >= 8; --bit) {
             const uint32_t trial = thr_bits | (1u << bit);
-            if (__popcll(__builtin_amdgcn_ballot_w64(mine >= trial)) >= n_eff) thr_bits = trial;
+            if (__popcll(__builtin_amdgcn_ballot_w64(best >= trial)) >= n_eff) thr_bits = trial;
         }
     }
     wave_lds_sync();      // the importance bits written above are read by other lanes below
@@ -204,10 +242,31 @@ __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l
             if (jb + 64 * u > J) break;               // uniform
             const bool is = j <= J && bits[u] >= thr_bits;
             const uint64_t m = __builtin_amdgcn_ballot_w64(is);
+            if (m == 0) continue;                     // uniform
             const int pos = n_cand + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
             if (is && pos < kWaveMaxCand) w.cand[pos] = topn_key(bits[u], j);
             n_cand += __popcll(m);
         }
+    }
+    if (n_cand <= 64) {
+        // One candidate per lane, in index order: the value of the n_eff-th largest, exactly, by bisection; the winners are
+        // the larger ones and the first of the equal ones, and their order is the output's: no ranking, no sorting.
+        wave_lds_sync();
+        const uint64_t key = lane < n_cand ? w.cand[lane] : 0ull;
+        const uint32_t bits = (uint32_t)(key >> 32);
+        uint32_t t = 0;
+        for (int bit = 31; bit >= 0; --bit) {
+            const uint32_t trial = t | (1u << bit);
+            if (__popcll(__builtin_amdgcn_ballot_w64(bits >= trial)) >= n_eff) t = trial;      // (trial > 0: no lane without a candidate)
+        }
+        auto before = [&](uint64_t m) { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
+        const bool gt = lane < n_cand && bits > t, eq = lane < n_cand && bits == t;
+        const int need = n_eff - __popcll(__builtin_amdgcn_ballot_w64(gt));
+        const bool win = gt || (eq && before(__builtin_amdgcn_ballot_w64(eq)) < need);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(win);
+        if (win) out[before(m)] = (int)(0xFFFFFFFFu - (uint32_t)key);
+        if (lane >= n_eff && lane < n_sel) out[lane] = -1;
+        return;
     }
     // pad the list to a multiple of 8 with keys that are larger than none (the counting loop below reads in eights)
     if (lane < 8 && n_cand + lane < kWaveMaxCand + 8) w.cand[min(n_cand, kWaveMaxCand) + lane] = 0ull;
@@ -227,18 +286,23 @@ __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l
         }
     } else {
         // massive ties: serial argmax, one winner per round; the owner (index mod 64) retires it and rescans
+        uint64_t best_key = 0;
+        for (int j = lane; j <= J; j += 64) {
+            const uint64_t key = topn_key(w.bits[j], j);
+            best_key = key > best_key ? key : best_key;
+        }
         for (int round = 0; round < n_eff; ++round) {
-            const uint64_t top = wave_max_u64(best);
+            const uint64_t top = wave_max_u64(best_key);
             const int j_top = (int)(0xFFFFFFFFu - (uint32_t)top);
             if (lane == 0) w.pick[round] = top ? j_top : 0;
             if (!top) continue;       // (cannot happen: there are at least n_eff blocks)
             if ((j_top & 63) == lane) {
                 w.bits[j_top] = 0xFFFFFFFFu;      // retired (no importance has this pattern)
-                best = 0;
+                best_key = 0;
                 for (int j = lane; j <= J; j += 64) {
                     const uint32_t bits = w.bits[j];
                     const uint64_t key = topn_key(bits, j);
-                    if (bits != 0xFFFFFFFFu && key > best) best = key;
+                    if (bits != 0xFFFFFFFFu && key > best_key) best_key = key;
                 }
             }
         }

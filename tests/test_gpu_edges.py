@@ -1,0 +1,45 @@
+"""Edges of the selection inside the selected-branch launch (groups of 64 blocks, 512 or 1024 blocks in flight, the
+remainder, ties) and of the matrix-core scan's two half-phases (slices of one to five tiles, a last tile of one row, no
+tile at all), against the oracle and against the selection's own launch, whose kernel is another one."""
+import numpy as np
+import pytest
+
+import ssv_inputs as si
+from test_gpu_parity import dev_mod, run_refresh  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d_k", [64, 192])
+@pytest.mark.parametrize("blocks", [1, 63, 64, 65, 66, 128, 130, 512, 513, 577, 1024, 1027, 1089, 2050])
+def test_selection_at_the_edges_of_its_groups(dev_mod, oracle, blocks, d_k):  # noqa: F811
+    from paper_2605_19893_amd import binding as B
+    d_v = 64 if d_k == 64 else 128
+    case = si.make_case(f"sel_edge_{blocks}_{d_k}", "bf16", 1, 3, 16, 1, d_k, d_v, si.STD_NSA, [blocks * 64 - 1], 301 + blocks, rho=0.3)
+    _, _, _, inside = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_IN_SLC)
+    _, _, _, own = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_SEPARATE)
+    assert np.array_equal(inside, own)
+
+
+@pytest.mark.parametrize("n_cmp", [0, 3, 255, 300, 3000])
+@pytest.mark.parametrize("n_init", [0, 1, 4])
+def test_selection_with_few_compressed_rows_is_one_of_ties(dev_mod, oracle, n_cmp, n_init):  # noqa: F811
+    """Blocks without a compressed row have importance 0: many candidates of the same value, the smaller indices win."""
+    from paper_2605_19893_amd import binding as B
+    nsa = si.NsaParams(l=32, d=16, l_sel=64, n_sel=16, w=512, n_init=n_init, n_local=2)
+    case = si.make_case(f"sel_ties_{n_cmp}_{n_init}", "f32", 1, 2, 4, 1, 64, 64, nsa, [70000], 401 + n_cmp)
+    case.n_cmp[:] = n_cmp
+    _, _, _, inside = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_IN_SLC)
+    _, _, _, own = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_SEPARATE)
+    assert np.array_equal(inside, own)
+
+
+@pytest.mark.parametrize("T", [12, 17])
+@pytest.mark.parametrize("rows", [0, 1, 63, 64, 65, 128, 129, 193, 257, 320])
+def test_matrix_scan_of_few_tiles(dev_mod, oracle, rows, T):  # noqa: F811
+    from paper_2605_19893_amd import binding as B
+    length = 32 + 16 * (rows - 1) if rows else 20
+    for name, lens, avg in (("even", [length], 0), ("balanced", [length, 900, length], None)):
+        case = si.make_case(f"scan_edge_{name}_{rows}_{T}", "bf16", len(lens), T, 16, 1, 192, 128, si.STD_NSA, lens, 501 + rows, rho=0.5,
+                            cmp_over_drafts=False)
+        run_refresh(dev_mod, oracle, case, scan_kernel=B.SSV_SCAN_MATRIX, avg_seq_len=avg)
