@@ -18,8 +18,8 @@
 //   in its vector phase.  (All in step, both wanted the same pipe at the same time, the loads held all eight up, and the
 //   compiler waited for the loads in flight before every P.V.)  4 sequences of 40 queries over 128K tokens: a tile takes
 //   4030 clocks instead of 5400, of which the matrix instructions are 2560; as both pipes work at once the clock falls from
-//   2.37 to 1.93 GHz, so that the launch gains less than that, 69.5 -> 66 us (a stream of these matrix instructions alone,
-//   on random data, runs at 1.65 GHz).  With 16 queries per sequence a tile is used once and the launch is at 4.3 TB/s.
+//   2.37 to 1.93 GHz, so that the launch gains less than that, 69.5 -> 66 us by dispatch events in alternating calls (a stream
+//   of these matrix instructions alone, on random data, runs at 1.65 GHz).  With 16 queries per sequence a tile is used once and the launch is at 4.3 TB/s.
 //
 //   The running maximum is a reference that is only raised when a tile's maximum exceeds it by more than 2^8
 //   (probabilities stay below 256: exact in the partial state's own terms, which carries the reference), so the
