@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "device_common.hpp"
+#include "topn_fold.hpp"
 
 namespace ssv {
 
@@ -97,7 +98,7 @@ __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l
     const int a_ratio = l_sel / d, b_ratio = l / d;
     const int n_eff = min(n_sel, J + 1);
     const int n_terms = a_ratio + b_ratio - 1;
-    const int j_last_scored = J - max(n_local, 0);
+    const int j_last_scored = fold_last_scored(J, n_local);
     uint32_t best = 0;         // largest importance among the blocks of this lane (index mod 64), as its bit pattern
     for (int j = max(j_last_scored + 1, 0); j <= J; ++j) {     // forced trailing local blocks, each with its owner lane
         if ((j & 63) != lane) continue;
@@ -112,10 +113,8 @@ __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l
         // 1024 blocks are in flight together.  (2048 blocks: 13 us of the selected launch of 40-node trees at 128K with the
         // conditions at every block and 512 in flight.)
         auto block_loads = [&](int j, f32x4& x, float& xm) {
-            const int c0 = j <= j_last_scored ? 4 * j : 0;
-            // (a row holds nc_pitch columns, a multiple of 64: a block starting past it has no visible column)
-            x = *reinterpret_cast<const f32x4*>(cs + (c0 < ncv ? c0 : 0));
-            xm = cs[(c0 >= 1 && c0 - 1 < ncv) ? c0 - 1 : 0];
+            x = *reinterpret_cast<const f32x4*>(cs + fold_column(j, j_last_scored, ncv));
+            xm = cs[fold_left_column(j, j_last_scored, ncv)];
         };
         auto put = [&](int j, float imp) {
             const uint32_t bits = j < n_init ? 0x7F800000u : __float_as_uint(imp);
@@ -133,8 +132,8 @@ __device__ __forceinline__ void wave_topn(const float* cs, int ncv, int J, int l
             if (c0 + 3 < ncv) imp += 1.f * x[3];
             put(j, imp);
         };
-        const int groups = min(j_last_scored + 1, ncv >> 2) >> 6;      // groups of 64 blocks with every column visible
-        constexpr int NR = 2;                                          // the remainder's loads go first (it rarely has more groups)
+        const int groups = fold_full_groups(j_last_scored, ncv);
+        constexpr int NR = 2;      // the remainder's loads go first (it rarely has more groups)
         f32x4 rx[NR];
         float rm[NR];
 #pragma unroll

@@ -1,6 +1,7 @@
-"""Address- and undefined-behaviour-sanitizer leg (CPU only): the C oracle and the library's host-only planner
-pieces are rebuilt with -fsanitize=address,undefined and driven through the brute-force and guard / flattening
-cases; any report aborts the run (-fno-sanitize-recover) and results must equal the plain builds'."""
+"""Address- and undefined-behaviour-sanitizer leg (CPU only): the C oracle, the library's host-only planner pieces and
+the index arithmetic of the in-launch selection are rebuilt with -fsanitize=address,undefined and driven through the
+brute-force, guard / flattening and fold cases; any report aborts the run (-fno-sanitize-recover) and results must equal the
+plain builds'."""
 import os
 import subprocess
 
@@ -119,3 +120,13 @@ def test_planner_under_sanitizers_matches_the_python_statement(planner_exe):
     assert r.returncode == 0, r.stderr[-3000:]
     got = [ln.strip() for ln in r.stdout.strip().split("\n")]
     assert got == want
+
+
+def test_selection_fold_stays_inside_its_arrays(tmp_path):
+    """Blocks and columns that the in-launch selection touches, for every position against every count of forced local
+    blocks (more of them than blocks among them) and at the edges of its groups: none outside the query's column row or its
+    importances, and every scored block gets its sum."""
+    exe = tmp_path / "fold_harness"
+    subprocess.check_call(["g++", "-std=c++17", "-Wall", "-Wextra", *SAN, os.path.join(HERE, "sanitize", "fold_harness.cpp"), "-o", str(exe)])
+    r = subprocess.run([str(exe)], env=ENV, capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout[-1000:] + r.stderr[-3000:]
