@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import ssv_inputs as si
+from parity import check, compare
 from test_gpu_parity import dev_mod, run_refresh  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
@@ -34,12 +35,33 @@ def test_selection_with_few_compressed_rows_is_one_of_ties(dev_mod, oracle, n_cm
     assert np.array_equal(inside, own)
 
 
+def takes_balanced_split(plan, max_n_cmp):
+    """Even slices of ntc tiles are ceil(ntc / slices) tiles each and none is superfluous; ranges of the balanced split cover the
+    longest sequence and its fixed cost with one slot to spare."""
+    return (plan.n_cmp_chunks - 1) * plan.tiles_per_chunk >= max(1, -(-max_n_cmp // 64))
+
+
 @pytest.mark.parametrize("T", [12, 17])
 @pytest.mark.parametrize("rows", [0, 1, 63, 64, 65, 128, 129, 193, 257, 320])
 def test_matrix_scan_of_few_tiles(dev_mod, oracle, rows, T):  # noqa: F811
+    """Even slices (of one sequence, of three); ranges of the balanced split that hold one tile each; and (one query per workgroup of the scan: fewer, longer
+    ranges) ranges that hold all tiles of one pair and go on into the next, with the same sequence's metadata and with another's."""
     from paper_2605_19893_amd import binding as B
     length = 32 + 16 * (rows - 1) if rows else 20
-    for name, lens, avg in (("even", [length], 0), ("balanced", [length, 900, length], None)):
-        case = si.make_case(f"scan_edge_{name}_{rows}_{T}", "bf16", len(lens), T, 16, 1, 192, 128, si.STD_NSA, lens, 501 + rows, rho=0.5,
+    long = length + 1100
+    for name, lens, H_kv, avg, scan_group in (("even", [length], 1, 0, 0), ("even_batch", [length, 900, length], 1, 0, 0),
+                                              ("short_ranges", [length, long, length], 1, 1, 0),
+                                              ("long_ranges", 4 * [length, long, length], 2, 1, 1)):
+        case = si.make_case(f"scan_edge_{name}_{rows}_{T}", "bf16", len(lens), T, 16 * H_kv, H_kv, 192, 128, si.STD_NSA, lens, 501 + rows, rho=0.5,
                             cmp_over_drafts=False)
-        run_refresh(dev_mod, oracle, case, scan_kernel=B.SSV_SCAN_MATRIX, avg_seq_len=avg)
+        assert int(case.n_cmp[0]) == rows
+        dev = dev_mod.DeviceCase(case, scan_kernel=B.SSV_SCAN_MATRIX, avg_seq_len=avg)
+        dev.set_group_size(0, B.SSV_REFRESH, scan_group_size=scan_group)
+        plan = dev.plan
+        assert plan.scan_matrix == 1 and takes_balanced_split(plan, int(case.n_cmp.max())) == name.endswith("ranges")
+        if name == "long_ranges":       # more pairs than ranges: some range holds more than one
+            assert len(lens) * H_kv > 256 // plan.n_qg_scan
+        print(f"[run] {case.name} plan={plan.as_dict()}", flush=True)
+        dev.run()
+        out, sel = dev.results()
+        check(case, compare(case, oracle, oracle.nsa_verify(case), out, sel))
