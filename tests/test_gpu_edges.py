@@ -11,14 +11,23 @@ from test_gpu_parity import dev_mod, run_refresh  # noqa: F401  (fixture)
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d_k", [64, 192])
-@pytest.mark.parametrize("blocks", [1, 63, 64, 65, 66, 128, 130, 512, 513, 577, 1024, 1027, 1089, 2050])
-def test_selection_at_the_edges_of_its_groups(dev_mod, oracle, blocks, d_k):  # noqa: F811
+def select_both_ways(dev_mod, oracle, case):
+    """The sets of the selection inside the selected-branch launch and of its own launch; the plan says that each is what ran
+    (importances that do not fit that launch's tile buffers are selected from in the launch of their own whatever the caller asks)."""
     from paper_2605_19893_amd import binding as B
+    dev, _, _, inside = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_IN_SLC)
+    assert dev.plan.topn_in_slc == 1
+    dev, _, _, own = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_SEPARATE)
+    assert dev.plan.topn_in_slc == 0
+    return inside, own
+
+
+@pytest.mark.parametrize("blocks,d_k", [(n, d) for n in (1, 63, 64, 65, 66, 128, 130, 512, 513, 577, 1024, 1027, 1089, 2050) for d in (64, 192)
+                                        if (n, d) != (2050, 64)])       # (that many importances do not fit at d_k = 64)
+def test_selection_at_the_edges_of_its_groups(dev_mod, oracle, blocks, d_k):  # noqa: F811
     d_v = 64 if d_k == 64 else 128
     case = si.make_case(f"sel_edge_{blocks}_{d_k}", "bf16", 1, 3, 16, 1, d_k, d_v, si.STD_NSA, [blocks * 64 - 1], 301 + blocks, rho=0.3)
-    _, _, _, inside = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_IN_SLC)
-    _, _, _, own = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_SEPARATE)
+    inside, own = select_both_ways(dev_mod, oracle, case)
     assert np.array_equal(inside, own)
 
 
@@ -26,12 +35,10 @@ def test_selection_at_the_edges_of_its_groups(dev_mod, oracle, blocks, d_k):  # 
 @pytest.mark.parametrize("n_init", [0, 1, 4])
 def test_selection_with_few_compressed_rows_is_one_of_ties(dev_mod, oracle, n_cmp, n_init):  # noqa: F811
     """Blocks without a compressed row have importance 0: many candidates of the same value, the smaller indices win."""
-    from paper_2605_19893_amd import binding as B
     nsa = si.NsaParams(l=32, d=16, l_sel=64, n_sel=16, w=512, n_init=n_init, n_local=2)
     case = si.make_case(f"sel_ties_{n_cmp}_{n_init}", "f32", 1, 2, 4, 1, 64, 64, nsa, [70000], 401 + n_cmp)
     case.n_cmp[:] = n_cmp
-    _, _, _, inside = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_IN_SLC)
-    _, _, _, own = run_refresh(dev_mod, oracle, case, topn_home=B.SSV_TOPN_SEPARATE)
+    inside, own = select_both_ways(dev_mod, oracle, case)
     assert np.array_equal(inside, own)
 
 
