@@ -253,16 +253,10 @@ struct DirectRowTile {
         }
     }
     // rsrc: buffer resource over the rows of one (sequence, KV head); tile_off: byte offset of the tile's first row
-    // RECOMPUTE: the (row, column) pairs behind the clamped offsets of a partial tile are derived again at every
-    // partial tile instead of being kept in registers across the caller's loops (for kernels short of registers).
-    template <bool RECOMPUTE = false>
     __device__ __forceinline__ void issue(u32x4 rsrc, uint32_t tile_off, char* lds_tile, uint32_t g_row_bytes,
                                           int valid_rows, int tid) {
         const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_addr(lds_tile) + (uint32_t)(tid >> 6) * ITERS * 1024u);
         const uint32_t soff = __builtin_amdgcn_readfirstlane(tile_off);
-        if constexpr (RECOMPUTE) {
-            if (valid_rows < kTile) asm volatile("" : "+v"(tid));    // opaque from here on: nothing below can be hoisted
-        }
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
             uint32_t o = off[it];
