@@ -136,6 +136,10 @@ __device__ __forceinline__ u32x4 lds_read16_at(uint32_t addr) {
 // counted wait in front, so that nothing is fetched ahead.  Its own counted waits become stricter by the loads it does not
 // know: callers let it wait for registers loaded earlier (arrived, below) before they issue what may stay in flight.
 // Five wait states between a scalar register written by a vector instruction and its use here, one behind m0.
+// m0 is a reserved register: the compiler does not promise to honour it in a clobber list.  A kernel that uses this function must
+// therefore have no other use of m0: no LDS load through a builtin, no other assembly that sets or reads it.  That holds for
+// k_stream, k_scan32 and k_importance32 (every m0 in their code is the one written here); k_importance, which uses the builtin,
+// does not use this function.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"       // (m0 in the clobber list)
 __device__ __forceinline__ void buffer_load_lds16(u32x4 rsrc, uint32_t lds, uint32_t voff, uint32_t soff) {
