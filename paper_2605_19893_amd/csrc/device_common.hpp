@@ -19,9 +19,13 @@ constexpr int kMaxT = 128;
 // Brings the kernel's argument block into the scalar cache in one memory round trip.  The compiler loads arguments where
 // they are first used, and at the start of a launch every 64-byte line of the block is a miss of its own (two or three lines
 // in the combine kernels).  Combine launches with it and without: 6.1 against 6.4 us, 8.8 / 9.1, 13.1 / 13.7 and 25.6 / 26.2;
-// no difference in the launches of 4 to 5 us, which wait longer for their statistics.  Before k_stream (six lines, the lengths
-// ahead of the query rows) calls of 35 to 60 us take 0.3 to 0.6 us less with it, but one that is a single launch (all three
-// branches) 0.2 more; the importance pass loses 0.7 us to it, the matrix-core scan does not mind.
+// no difference in the launches of 4 to 5 us, which wait longer for their statistics.  In k_stream (six lines, the lengths
+// ahead of the query rows), whole calls without it and with it, two runs each that differ by 0.1 to 0.2 %: one row tile per
+// wave: chain of eight at 32K 34.8 -> 34.1 us, batches of ragged lengths 43.9 -> 43.5, 2K fp32 29.7 -> 29.5, 16 sequences at
+// 64K 110.1 -> 109.9, 64 queries at d = 64 no difference; a reuse call of a single launch (all three branches) 16.15 ->
+// 16.35; two row tiles per wave (longer launches, whose query rows wait for the metadata anyway): 8 queries of 16 heads at 64K
+// 137.1 -> 137.6, 16 of 8 heads at d = 128 96.3 -> 96.8, fp32 no difference.  So one row tile, and not the single launch.  The
+// importance pass loses 0.7 us to it, the matrix-core scan does not mind.
 template <typename Args>
 __device__ __forceinline__ void touch_args() {
     const auto* p = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();

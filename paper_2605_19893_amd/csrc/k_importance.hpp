@@ -428,8 +428,10 @@ __global__ void __launch_bounds__(kThreads, 2) k_importance(const ImportanceArgs
 }
 
 // ---- bf16 variant on the 32x32x16 matrix instruction ------------------------------------------------------------
-// Measured on the device, independent v_mfma_f32_16x16x32_bf16 sustain about half of the chip's bf16 matrix peak
-// and v_mfma_f32_32x32x16_bf16 all of it, so the bf16 pass takes its products in 32-row x 32-key blocks.
+// The bf16 pass takes its products in 32-row x 32-key blocks: v_mfma_f32_32x32x16_bf16 and v_mfma_f32_16x16x32_bf16 run at the
+// same rate (32.0 and 16.5 clocks from one wavefront, dependent or not; 2.1 to 2.3 PFLOP/s over the chip on zeros, 1.7 to 2.1 on
+// random data, where the clock falls below 2.1 GHz), but the larger block needs half the operand bytes from LDS and half the issue
+// slots for the same products.
 //   A operand = Q (lane l: row l % 32, the eight contraction elements 8 (l / 32) .. + 7 of a 16-element step),
 //   B operand = K (lane l: key l % 32, same elements), result lane l: key l % 32, rows 8 j + 4 (l / 32) + r at
 //   vector index 4 j + r: the rows of one lane are heads, so the head sum stays in the lane except for one exchange
@@ -752,8 +754,9 @@ k_importance32(const ImportanceArgs a) {
     // Software pipeline over the tiles of the slice.  Step `tile`: wait for the loads this wavefront issued for it
     // (younger operations on the in-order counter: the LD loads of the next tile and the stores of the two steps
     // since); the barrier then says the whole tile has landed and every wavefront has left tile - 1, whose ring slot
-    // the loads of tile + 2 may overwrite.  Inside a step the products of the next block are issued before the
-    // exponentials of the current one, so the matrix pipe works while the vector pipe finishes a block.
+    // the loads of tile + 2 may overwrite.  Inside a step, with two key tiles and two wavefronts per SIMD, the exponentials
+    // of the first block are spread between the products of the second; otherwise a wavefront takes block after block and the
+    // other wavefronts of its SIMD fill the gaps.
     for (int tile = t0; tile < t1; ++tile) {
         if (tile + 1 >= t1) wait_vmcnt<0>();
         else if (tile - t0 < 2) wait_vmcnt<LD>();

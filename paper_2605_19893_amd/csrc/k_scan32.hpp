@@ -305,14 +305,15 @@ __global__ void __launch_bounds__(kScan32Threads, 1) __attribute__((amdgpu_waves
 
         // Between two phases.  Into the even phase of tile t: K(t) and V(t - 1) have landed (they were issued two tiles ago;
         // loads complete in issue order, and only K(t + 1) and V(t) were issued since), and every wavefront has left
-        // K(t - 1) and V(t - 2), whose places the matrix phase of tile t fills with K(t + 2) and V(t + 1).
+        // K(t - 1) and V(t - 2), whose places K(t + 2) and V(t + 1) take: the loads that issue_ahead(t) issues.
         auto boundary = [&](bool into_even) {
             if (into_even) wait_vmcnt<KI + VI>();
             __syncthreads();
             __builtin_amdgcn_sched_barrier(0);
         };
-        // The loads of tile t's even phase.  They are issued by the half that is in its vector phase: the vector memory pipe
-        // takes 64 B per clock, so the 20 instructions of a phase take 330 clocks, which a matrix phase would spend waiting.
+        // The loads whose places are free from the even phase of tile t on.  Each half issues its share in its vector phase (the
+        // early half that of tile t, the late half, one phase behind, that of tile t + 1): the vector memory pipe takes 64 B per
+        // clock, so the 20 instructions of a phase take 330 clocks, which a matrix phase would spend waiting.
         auto issue_ahead = [&](int t) {
             prepare_k(t + 2);
             prepare_v(t + 1);
